@@ -94,16 +94,16 @@ void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int64_t total,
 
 // Front end: DMRS generation, LS pair estimates, interpolation + feature rows.
 // slot_mask (nullable, device, one word per slot): when given, slots whose word is 0 are skipped.
-void launch_dmrs(const SlotGeo *geo, int n_slots, float2 *dmrs, hipStream_t st,
-                 const unsigned int *slot_mask = nullptr);
-void launch_ls_pairs(const SlotGeo *geo, int n_slots, int max_pairs_total, const float2 *y,
-                     const float2 *dmrs, float2 *pairs, const int64_t *pair_off, int max_u_b_pairs,
-                     hipStream_t st, const unsigned int *slot_mask = nullptr);
+void launch_dmrs(const SlotGeo *geo, int n_slots, float2 *dmrs, hipStream_t st);
+void launch_ls_pairs(const SlotGeo *geo, int n_slots, int max_pairs_total, const float2 *y, float2 *pairs,
+                     const int64_t *pair_off, hipStream_t st, const unsigned int *slot_mask = nullptr);
+// the interpolated estimate alone, in the h layout (max_h: most entries of a slot)
+void launch_estimate(const SlotGeo *geo, int n_slots, int64_t max_h, const float2 *pairs, const int64_t *pair_off,
+                     float2 *h_out, hipStream_t st);
 template <typename T>
-void launch_features(const SlotGeo *geo, const int64_t *re_base, int n_slots, int64_t n_re,
-                     const float2 *y, const float2 *pairs, const int64_t *pair_off, int model_B,
-                     int cx, T *X, float2 *h_out, hipStream_t st, const unsigned int *slot_mask = nullptr,
-                     unsigned int *slot_flags = nullptr);   // OR-ed with 4 for a slot whose y is not all finite
+void launch_features(const SlotGeo *geo, int n_slots, int64_t max_rows, const float2 *y, const float2 *pairs,
+                     const int64_t *pair_off, int model_B, int cx, T *X, float2 *h_out, hipStream_t st,
+                     unsigned int *slot_flags);   // OR-ed with 4 for a slot whose y is not all finite
 
 // Message passing and readout.
 template <typename T>
@@ -144,11 +144,11 @@ void launch_stamp_latency(const unsigned long long *stamps, int n_slots, double 
 template <typename T>
 void launch_readout(const MlpArgs<T> &a, int grid, hipStream_t st);
 
-// LMMSE + max-log judge.
+// LMMSE + max-log judge, with the channel estimate h, or (h null) the LS estimate interpolated from pairs.
 // slot_mask (nullable): only slots with a non-zero word are demapped, and their LLRs that are not finite
 // are written as 0 (the fallback of a flagged NRX slot).
-void launch_lmmse(const SlotGeo *geo, const int64_t *re_base, int n_slots, int64_t n_re, int m_max,
-                  const float2 *y, const float2 *h, const float *n0dev, float *llr, hipStream_t st,
+void launch_lmmse(const SlotGeo *geo, int n_slots, int64_t max_re, int m_max, const float2 *y, const float2 *h,
+                  const float2 *pairs, const int64_t *pair_off, const float *n0dev, float *llr, hipStream_t st,
                   const unsigned int *slot_mask = nullptr);
 
 // Persistent forward (BF16 inference): one launch runs every layer of the CGNN over every slot.

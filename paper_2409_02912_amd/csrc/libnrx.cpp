@@ -116,12 +116,10 @@ struct Plan {
   size_t off_ctm[NRX_N_MODS][N_TILE_SIZES] = {}, off_rtm[NRX_N_MODS] = {};
   std::vector<char> blob;        // host image of the device tables
   void *pinned = nullptr;        // pinned copy, allocated on first upload
-  void *packed_geo = nullptr;    // lmmse_demap: pinned geometry copy with h offsets into its workspace
   ~Plan() {
     // an asynchronous copy (or a graph replay) may still read the pinned tables
-    if (pinned || packed_geo) (void)hipDeviceSynchronize();
+    if (pinned) (void)hipDeviceSynchronize();
     if (pinned) (void)hipHostFree(pinned);
-    if (packed_geo) (void)hipHostFree(packed_geo);
   }
 };
 using PlanRef = std::shared_ptr<Plan>;
@@ -777,7 +775,7 @@ std::vector<int> iteration_ends(const nrx_model_config &c) {
 }
 
 struct FwdLayout {
-  size_t meta, jobs, wprep, fields, dmrs, pairs, X, done, stamps, flags;   // the same for save and inference
+  size_t meta, jobs, wprep, fields, pairs, X, done, stamps, flags;   // the same for save and inference
   size_t pstages = 0, pctl = 0;   // persistent forward (model flags bit 3, inference): stage table, control words
   size_t h8 = 0, a8 = 0, agg8 = 0, w8 = 0, wsc = 0, f8jobs = 0, amax = 0;   // FP8 models
   std::vector<size_t> h;      // h_0 .. h_C (inference: one buffer)
@@ -807,7 +805,6 @@ FwdLayout fwd_layout(const nrx_model *m, const Plan *P, bool save) {
   L.jobs = o; o = align256(o + sizeof(PrepJob) * m->jobs.size());
   L.wprep = o; o = align256(o + (size_t)m->prep_elems * ts);
   L.fields = o; o = align256(o + (size_t)std::max<int64_t>(m->field_elems, 1) * 4);
-  L.dmrs = o; o = align256(o + (size_t)P->dmrs_total * 8);
   L.pairs = o; o = align256(o + (size_t)P->pairs_total * 8);
   L.X = o; o = align256(o + (size_t)P->rows * m->cx * ts);
   L.done = o; o = align256(o + (size_t)P->n * 4);
@@ -957,7 +954,6 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
   const Dev D = dev_tables(P, ws + L.meta);
   T *wprep = (T *)(ws + L.wprep);
   float *fields = (float *)(ws + L.fields);
-  float2 *dmrs = (float2 *)(ws + L.dmrs);
   float2 *pairs = (float2 *)(ws + L.pairs);
   T *X = (T *)(ws + L.X);
   unsigned int *slot_flags = (unsigned int *)(ws + L.flags);
@@ -965,10 +961,9 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
   {
     ProfMark pm(m, NRX_K_FRONTEND, st);
     launch_prep<T>(w, (const PrepJob *)(ws + L.jobs), (int)m->jobs.size(), m->prep_total, wprep, fields, st);
-    launch_dmrs(D.geo, P->n, dmrs, st);
-    launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, dmrs, pairs, D.pair_off, 0, st);
-    launch_features<T>(D.geo, nullptr, P->n, P->max_rows, (const float2 *)y, pairs, D.pair_off, m->cfg.n_ant, m->cx,
-                       X, (float2 *)h_ls, st, nullptr, slot_flags);
+    launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st);
+    launch_features<T>(D.geo, P->n, P->max_rows, (const float2 *)y, pairs, D.pair_off, m->cfg.n_ant, m->cx, X,
+                       (float2 *)h_ls, st, slot_flags);
   }
   // FP8 models: E4M3 block-conv operands (or, while calibrating, BF16 convs that record max |activation|)
   const bool f8 = m->fp8 && !m->calibrating && !save;
@@ -1893,22 +1888,23 @@ extern "C" nrx_status nrx_backward_chest(nrx_model *m, const float *w, const nrx
 // --------------------------------------------------------- model-free calls --
 
 namespace {
+// Workspace of the classical calls.  Callers size it once and keep it, so its size stays what it was when the
+// DMRS sequences (now made where they are used) and the interpolated estimate were stored in it too.
 struct FrontLayout {
-  size_t meta, dmrs, pairs, h, total;
+  size_t meta, pairs, total;
 };
 FrontLayout front_layout(const Plan *P, bool need_h) {
   FrontLayout L;
   size_t o = 0;
   L.meta = o; o = align256(o + P->meta_bytes);
-  L.dmrs = o; o = align256(o + (size_t)P->dmrs_total * 8);
   L.pairs = o; o = align256(o + (size_t)P->pairs_total * 8);
+  o = align256(o + (size_t)P->dmrs_total * 8);
   int64_t hel = 0;
   for (auto &g : P->geo) hel += (int64_t)g.S * 14 * g.U * g.B;
-  L.h = o; o = align256(o + (need_h ? (size_t)hel * 8 : 0));
+  o = align256(o + (need_h ? (size_t)hel * 8 : 0));
   L.total = o;
   return L;
 }
-// internal LS estimates use a packed h layout: slot offsets are recomputed
 }  // namespace
 
 extern "C" size_t lmmse_workspace_bytes(const nrx_slot_desc *slots, int32_t n) {
@@ -1916,19 +1912,6 @@ extern "C" size_t lmmse_workspace_bytes(const nrx_slot_desc *slots, int32_t n) {
   if (get_plan(slots, n, 16, 8, 0, &PR) != NRX_OK) return 0;
   Plan *P = PR.get();
   return front_layout(P, true).total + align256(sizeof(SlotGeo) * (size_t)n);
-}
-
-static nrx_status ls_into(const Plan *P, const FrontLayout &L, const float *y, float *h, const SlotGeo *geo_h,
-                          char *ws, hipStream_t st, const unsigned int *slot_mask = nullptr) {
-  const Dev D = dev_tables(P, ws + L.meta);
-  float2 *dmrs = (float2 *)(ws + L.dmrs);
-  float2 *pairs = (float2 *)(ws + L.pairs);
-  launch_dmrs(D.geo, P->n, dmrs, st, slot_mask);
-  launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, dmrs, pairs, D.pair_off, 0, st, slot_mask);
-  launch_features<float>(geo_h ? geo_h : D.geo, nullptr, P->n, P->max_rows, (const float2 *)y, pairs, D.pair_off, 16,
-                         0, (float *)nullptr, (float2 *)h, st, slot_mask);
-  HIPCHK(hipGetLastError());
-  return NRX_OK;
 }
 
 extern "C" nrx_status nrx_ls_estimate(const nrx_slot_desc *slots, int32_t n, const float *y, float *h, void *ws,
@@ -1940,8 +1923,16 @@ extern "C" nrx_status nrx_ls_estimate(const nrx_slot_desc *slots, int32_t n, con
   if (s != NRX_OK) return s;
   const FrontLayout L = front_layout(P, false);
   if (ws_bytes < L.total) return fail(NRX_ERR_WORKSPACE, "workspace %zu < required %zu bytes", ws_bytes, L.total);
-  if (plan_upload(P, (char *)ws + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
-  return ls_into(P, L, y, h, nullptr, (char *)ws, st);
+  char *w = (char *)ws;
+  if (plan_upload(P, w + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
+  const Dev D = dev_tables(P, w + L.meta);
+  float2 *pairs = (float2 *)(w + L.pairs);
+  int64_t max_h = 0;
+  for (auto &g : P->geo) max_h = std::max(max_h, (int64_t)g.S * 14 * g.U * g.B);
+  launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st);
+  launch_estimate(D.geo, P->n, max_h, pairs, D.pair_off, (float2 *)h, st);
+  HIPCHK(hipGetLastError());
+  return NRX_OK;
 }
 
 
@@ -1962,35 +1953,9 @@ nrx_status lmmse_impl(const nrx_slot_desc *slots, int32_t n, int32_t m_max, cons
   char *w = (char *)ws;
   if (plan_upload(P, w + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w + L.meta);
-  const SlotGeo *geo = D.geo;
-  const float *hh = h;
-  if (!h) {
-    // packed internal estimate: a geometry copy with h offsets into the workspace buffer
-    void *pg;
-    {
-      std::lock_guard<std::mutex> lk(g_plans.mu);
-      if (!P->packed_geo) {
-        if (hipHostMalloc(&pg, sizeof(SlotGeo) * n, hipHostMallocDefault) != hipSuccess)
-          return fail(NRX_ERR_HIP, "hipHostMalloc failed");
-        SlotGeo *gp = (SlotGeo *)pg;
-        int64_t off = 0;
-        for (int i = 0; i < n; ++i) {
-          gp[i] = P->geo[i];
-          gp[i].h_off = off;
-          off += (int64_t)gp[i].S * 14 * gp[i].U * gp[i].B;
-        }
-        P->packed_geo = pg;
-      }
-      pg = P->packed_geo;
-    }
-    SlotGeo *gdev = (SlotGeo *)(w + L.total);
-    HIPCHK(hipMemcpyAsync(gdev, pg, sizeof(SlotGeo) * n, hipMemcpyHostToDevice, st));
-    s = ls_into(P, L, y, (float *)(w + L.h), gdev, w, st, slot_mask);
-    if (s != NRX_OK) return s;
-    geo = gdev;
-    hh = (const float *)(w + L.h);
-  }
-  launch_lmmse(geo, nullptr, P->n, P->max_re, m_max, (const float2 *)y, (const float2 *)hh, n0dev, llr, st,
+  float2 *pairs = (float2 *)(w + L.pairs);
+  if (!h) launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st, slot_mask);
+  launch_lmmse(D.geo, P->n, P->max_re, m_max, (const float2 *)y, (const float2 *)h, pairs, D.pair_off, n0dev, llr, st,
                slot_mask);
   HIPCHK(hipGetLastError());
   return NRX_OK;
@@ -2012,8 +1977,7 @@ extern "C" nrx_status nrx_fallback_lmmse(const nrx_slot_desc *slots, int32_t n, 
 // ------------------------------------------------ allocation-free judge --
 //
 // lmmse_demap_noalloc runs the kernels of lmmse_demap with every buffer they need beyond y, h and llr
-// (the per-slot tables, the DMRS sequences, the LS pair estimates and the interpolated LS estimate)
-// carved out of one file-scope device array, so the call allocates nothing: no hipMalloc, no pinned
+// (the per-slot tables and the LS pair estimates) carved out of one file-scope device array, so the call allocates nothing: no hipMalloc, no pinned
 // host staging, no plan-cache entry.  Each device holds its own copy of the array; its address is
 // taken once per device with hipGetSymbolAddress, and only that address reaches kernels and copies.
 
@@ -2041,10 +2005,12 @@ nrx_status scratch_of_current_device(char **out) {
   return NRX_OK;
 }
 
-// Scratch layout of one call: [SlotGeo n][pair offsets n+1][DMRS][LS pairs][interpolated LS estimate].
+// Scratch layout of one call: [SlotGeo n][pair offsets n+1][LS pairs].  The total, which decides the batches that
+// are refused, counts the DMRS sequences and the interpolated LS estimate as well: the limit stays where it was
+// when they were stored.
 struct NoAllocLayout {
-  size_t geo, pair_off, dmrs, pairs, h, total;
-  int64_t max_re, max_pairs, max_rows;
+  size_t geo, pair_off, pairs, total;
+  int64_t max_re, max_pairs;
 };
 NoAllocLayout noalloc_layout(const nrx_slot_desc *d, int n, bool need_h) {
   NoAllocLayout L{};
@@ -2056,14 +2022,13 @@ NoAllocLayout noalloc_layout(const nrx_slot_desc *d, int n, bool need_h) {
     hel += S * 14 * U * B;
     L.max_re = std::max(L.max_re, S * 14);
     L.max_pairs = std::max(L.max_pairs, 2 * U * (S / 4) * B);
-    L.max_rows = std::max(L.max_rows, S * 14 * U);
   }
   size_t o = 0;
   L.geo = o; o = align256(o + sizeof(SlotGeo) * (size_t)n);
   L.pair_off = o; o = align256(o + sizeof(int64_t) * (size_t)(n + 1));
-  L.dmrs = o; o = align256(o + (size_t)dmrs * 8);
   L.pairs = o; o = align256(o + (size_t)pairs * 8);
-  L.h = o; o = align256(o + (need_h ? (size_t)hel * 8 : 0));
+  o = align256(o + (size_t)dmrs * 8);
+  o = align256(o + (need_h ? (size_t)hel * 8 : 0));
   L.total = o;
   return L;
 }
@@ -2086,14 +2051,14 @@ extern "C" nrx_status lmmse_demap_noalloc(const nrx_slot_desc *slots, int32_t n,
                 (size_t)NRX_NOALLOC_SCRATCH_BYTES);
   char *w = nullptr;
   if (nrx_status v = scratch_of_current_device(&w)) return v;
-  // host image of the tables; the internal estimate is packed slot after slot in the scratch
-  const size_t tbytes = L.dmrs;
+  // host image of the tables
+  const size_t tbytes = L.pairs;
   thread_local std::vector<char> img;
   if (img.size() < tbytes) img.resize(tbytes);
   std::fill(img.begin(), img.begin() + tbytes, 0);
   SlotGeo *geo = (SlotGeo *)(img.data() + L.geo);
   int64_t *poff = (int64_t *)(img.data() + L.pair_off);
-  int64_t dm = 0, pr = 0, ho = 0;
+  int64_t dm = 0, pr = 0;
   for (int i = 0; i < n; ++i) {
     const nrx_slot_desc &s = slots[i];
     SlotGeo g{};
@@ -2107,7 +2072,7 @@ extern "C" nrx_status lmmse_demap_noalloc(const nrx_slot_desc *slots, int32_t n,
     g.n0 = s.n0;
     g.snr_off = s.snr_offset_db;
     g.y_off = s.y_offset;
-    g.h_off = h ? s.h_offset : ho;
+    g.h_off = s.h_offset;
     g.llr_off = s.llr_offset;
     g.bits_off = s.bits_offset;
     g.dmrs_off = dm;
@@ -2115,25 +2080,15 @@ extern "C" nrx_status lmmse_demap_noalloc(const nrx_slot_desc *slots, int32_t n,
     poff[i] = pr;
     dm += g.S;
     pr += 2LL * g.U * (g.S / 4) * g.B;
-    ho += (int64_t)g.S * 14 * g.U * g.B;
   }
   poff[n] = pr;
   // pageable source: the copy has read the host image when hipMemcpyAsync returns
   HIPCHK(hipMemcpyAsync(w, img.data(), tbytes, hipMemcpyHostToDevice, st));
   const SlotGeo *dgeo = (const SlotGeo *)(w + L.geo);
   const int64_t *dpoff = (const int64_t *)(w + L.pair_off);
-  const float *hh = h;
-  if (!h) {
-    float2 *dmrs = (float2 *)(w + L.dmrs);
-    float2 *pairs = (float2 *)(w + L.pairs);
-    launch_dmrs(dgeo, n, dmrs, st);
-    launch_ls_pairs(dgeo, n, (int)L.max_pairs, (const float2 *)y, dmrs, pairs, dpoff, 0, st);
-    launch_features<float>(dgeo, nullptr, n, L.max_rows, (const float2 *)y, pairs, dpoff, 16, 0, (float *)nullptr,
-                           (float2 *)(w + L.h), st);
-    HIPCHK(hipGetLastError());
-    hh = (const float *)(w + L.h);
-  }
-  launch_lmmse(dgeo, nullptr, n, L.max_re, m_max, (const float2 *)y, (const float2 *)hh, n0dev, llr, st);
+  float2 *pairs = (float2 *)(w + L.pairs);
+  if (!h) launch_ls_pairs(dgeo, n, (int)L.max_pairs, (const float2 *)y, pairs, dpoff, st);
+  launch_lmmse(dgeo, n, L.max_re, m_max, (const float2 *)y, (const float2 *)h, pairs, dpoff, n0dev, llr, st);
   HIPCHK(hipGetLastError());
   return NRX_OK;
 }

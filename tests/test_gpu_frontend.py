@@ -1,0 +1,85 @@
+"""GPU parity of the DMRS sequence, the LS estimate and the LMMSE receiver at the edges of their tiles, against the
+fp64 oracle: bandwidths of one PRB to the largest (a remainder of the 16-subcarrier workgroups, every length of
+sequence), every UE count, odd and single antennas, slots of different sizes in one batch, scrambling identities.
+
+Bars: the LS estimate is a sum of two products and an interpolation in fp32, 1e-6 norm-wise.  LMMSE LLRs: the solve
+is fp64 on an fp32 estimate, whose rounding (6e-8) the max-log distances scale by at most the channel's condition
+number; 1e-5 norm-wise as for every other LMMSE test."""
+import numpy as np
+import pytest
+
+from nrx_cases import log, oracle_batch, pack_complex, rel_err, sim_cfg_oracle, split_h, split_llr
+from oracle import nr, receiver
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+L = pytest.importorskip("paper_2409_02912_amd.libnrx")
+CFG = dict(n_taps=4, decay_ns=100.0, doppler=20.0, rho=0.0, snr=(5.0, 15.0))
+
+
+def _shape(prb, ant, ue, bits, num, n_id=0, scid=0):
+    return dict(n_prb=prb, n_ant=ant, n_ue=ue, bits=bits, slot_number=num, n_id=n_id, n_scid=scid)
+
+
+BATCHES = {
+    "one-prb": [_shape(1, 1, 1, [2], 0), _shape(1, 5, 4, [2, 4, 6, 8], 19, 65535)],
+    "remainders": [_shape(3, 3, 3, [8, 2, 4], 7, 1), _shape(5, 16, 2, [6, 8], 3), _shape(4, 2, 1, [4], 11, 77)],
+    "largest": [_shape(275, 2, 1, [2], 5, 9), _shape(2, 4, 4, [4, 4, 4, 4], 6)],
+}
+
+
+def _oracle(shapes, seed):
+    return oracle_batch(shapes, sim_cfg_oracle(CFG), seed, 0, 8)
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_ls_estimate_edges(name):
+    shapes = BATCHES[name]
+    log(f"ls_estimate edges: {name}")
+    ref = _oracle(shapes, 21)
+    descs, sz = L.make_slots(shapes, 8)
+    y = torch.from_numpy(pack_complex([r["y32"] for r in ref])).cuda()
+    h = torch.full((2 * sz["h"],), float("nan"), device="cuda")
+    ws = torch.empty(L.lmmse_workspace_bytes(descs), dtype=torch.uint8, device="cuda")
+    L.nrx_ls_estimate(descs, y, h, ws)
+    torch.cuda.synchronize()
+    for got, r in zip(split_h(h.cpu().numpy().view(np.complex64), shapes), ref):
+        assert rel_err(got, receiver.ls_estimate(r["y32"], r["desc"])) < 1e-6
+
+
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_lmmse_edges(name, given):
+    log(f"lmmse edges: {name}, estimate given: {given}")
+    ref = _oracle(BATCHES[name], 22)
+    shapes = [dict(s, n0=r["n0_32"]) for s, r in zip(BATCHES[name], ref)]
+    descs, sz = L.make_slots(shapes, 8)
+    y = torch.from_numpy(pack_complex([r["y32"] for r in ref])).cuda()
+    hls = [receiver.ls_estimate(r["y32"], r["desc"]) for r in ref]
+    h = torch.from_numpy(pack_complex(hls)).cuda() if given else None
+    llr = torch.full((sz["llr"],), float("nan"), device="cuda")
+    ws = torch.empty(L.lmmse_workspace_bytes(descs), dtype=torch.uint8, device="cuda")
+    L.lmmse_demap(descs, 8, y, llr, ws, h=h)
+    torch.cuda.synchronize()
+    for got, hr, r in zip(split_llr(llr.cpu().numpy(), shapes, 8), hls, ref):
+        exp = receiver.lmmse_demap(r["y32"], hr, r["n0_32"], r["desc"], 8)
+        for u in range(exp.shape[0]):
+            assert rel_err(got[u], exp[u]) < 1e-5, u
+            assert np.all(got[u][:, :, r["desc"].bits_per_sym[u]:] == 0)
+        assert np.all(got[:, list(nr.DMRS_SYMBOLS)] == 0)
+
+
+def test_nothing_beside_the_batch_is_written():
+    """The LLR array is exactly covered: guard words on both sides of a one-PRB slot keep their values."""
+    shapes = [_shape(1, 2, 3, [2, 4, 2], 2)]
+    ref = _oracle(shapes, 23)
+    descs, sz = L.make_slots([dict(shapes[0], n0=0.1)], 4)
+    descs[0].llr_offset = 5
+    y = torch.from_numpy(pack_complex([r["y32"] for r in ref])).cuda()
+    llr = torch.full((sz["llr"] + 64,), 7.0, device="cuda")
+    ws = torch.empty(L.lmmse_workspace_bytes(descs), dtype=torch.uint8, device="cuda")
+    L.lmmse_demap(descs, 4, y, llr, ws)
+    torch.cuda.synchronize()
+    out = llr.cpu().numpy()
+    assert np.all(out[:5] == 7.0) and np.all(out[5 + sz["llr"]:] == 7.0)
+    assert not np.any(out[5:5 + sz["llr"]] == 7.0)
