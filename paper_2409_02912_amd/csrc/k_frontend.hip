@@ -109,9 +109,10 @@ __global__ __launch_bounds__(256) void ls_pairs_kernel(const SlotGeo *geo, const
       const float w = ((u & 1) && kp == 1) ? -1.f : 1.f;
       const float2 p = dmrs_value(x, 2 * n + kp);
       const float2 v = y[g.y_off + ((int64_t)k * 14 + l) * B + b];
-      // y * conj(w p)
-      hr += w * (v.x * p.x + v.y * p.y);
-      hi += w * (v.y * p.x - v.x * p.y);
+      // y * conj(w p); the fused products are spelled out, so that the estimate, whose last bit a 16-bit network
+      // carries into its LLRs, does not depend on the compiler's choice
+      hr = fmaf(w, fmaf(v.x, p.x, v.y * p.y), hr);
+      hi = fmaf(w, fmaf(v.y, p.x, -(v.x * p.y)), hi);
     }
     dst[e] = make_float2(0.5f * hr, 0.5f * hi);
   }

@@ -24,12 +24,13 @@ __device__ __forceinline__ LsPoint ls_point(int s, int t, int delta, int np) {
   return q;
 }
 
+// (fused products spelled out: every user of the estimate gets the same bits)
 __device__ __forceinline__ float2 ls_mix(const LsPoint &q, const float2 (&a0)[2], const float2 (&a1)[2]) {
   float2 hl[2];
 #pragma unroll
   for (int li = 0; li < 2; ++li)
-    hl[li] = make_float2((1.f - q.w) * a0[li].x + q.w * a1[li].x, (1.f - q.w) * a0[li].y + q.w * a1[li].y);
-  return make_float2(q.wt0 * hl[0].x + q.wt1 * hl[1].x, q.wt0 * hl[0].y + q.wt1 * hl[1].y);
+    hl[li] = make_float2(fmaf(1.f - q.w, a0[li].x, q.w * a1[li].x), fmaf(1.f - q.w, a0[li].y, q.w * a1[li].y));
+  return make_float2(fmaf(q.wt0, hl[0].x, q.wt1 * hl[1].x), fmaf(q.wt0, hl[0].y, q.wt1 * hl[1].y));
 }
 
 // estimate of UE u at antenna b from the slot's pairs P
