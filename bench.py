@@ -179,7 +179,7 @@ CONV_VARIANT_KERNELS = [
     "conv3x3_ring_kernel<MB 4, NW 8, G 3, OCC 1, NBUF 2, staggered start>",
     "conv3x3_ring_kernel<MB 4, NW 8, G 3, OCC 1, NBUF 2, raised wave priority, staggered start>",
     "conv3x3_ring_kernel<MB 4, NW 8, G 3, OCC 1, NBUF 3, 504-row subcarrier-aligned tiles>",
-    "conv3x3_ring_kernel<MB 4, NW 8, G 3, OCC 1, NBUF 2, falling wave priority>",
+    "conv3x3_ring_kernel<MB 4, NW 8, G 3, OCC 1, 7 tap slots, falling wave priority>",
 ]
 
 

@@ -69,8 +69,9 @@ struct Fp8Job {
 };
 void launch_prep_fp8(const float *w, const Fp8Job *jobs, int n_jobs, uint8_t *w8, float *wscale, hipStream_t st);
 
+// mb: rows per wave / 16 of the default variant (tiles of 128 mb rows); the others have a fixed tile
 template <typename T>
-void launch_conv(const ConvArgs<T> &a, int epi, int variant, int grid, hipStream_t st);
+void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, hipStream_t st);
 
 // Weight preparation: fp32 master -> MFMA operand layouts and PE fields.
 struct PrepJob {

@@ -373,13 +373,18 @@ __global__ __launch_bounds__(64 * NW, 1) void conv3x3_lds_kernel(ConvArgs<T> a) 
 // two 256-row workgroups share a CU, so one workgroup's epilogue overlaps the other's MFMAs.
 template <typename T, int EPI, int MB, int NW, int G, int OCC, int NBUF, int SCHED, int STAG, int ALIGNED>
 __global__ __launch_bounds__(64 * NW, OCC) void conv3x3_ring_kernel(ConvArgs<T> a) {
-  using Sh = RingShape<MB, NW, G, NBUF, ALIGNED>;
+  using Sh = typename std::conditional<SCHED == 4, PipeShape<MB, NW>, RingShape<MB, NW, G, NBUF, ALIGNED>>::type;
   __shared__ __align__(16) unsigned char lds[Sh::LDS_BYTES];
   float lnp[EPI == EPI_LN_BWD ? 16 : 1];
 #pragma unroll
   for (int k = 0; k < (EPI == EPI_LN_BWD ? 16 : 1); ++k) lnp[k] = 0.f;
-  conv_ring_body<T, EPI, MB, NW, G, NBUF, SCHED, GridTiles, STAG, ALIGNED>(a, GridTiles(a.tiles, a.n_tiles),
-                                                                           (lds_u8 *)lds, lnp);
+  if constexpr (SCHED == 4) {
+    static_assert(G == 3 && NBUF == TAP_SLOTS && !STAG && !ALIGNED, "pipe variant");
+    conv_pipe_body<T, EPI, MB, NW>(a, GridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds, lnp);
+  } else {
+    conv_ring_body<T, EPI, MB, NW, G, NBUF, SCHED, GridTiles, STAG, ALIGNED>(a, GridTiles(a.tiles, a.n_tiles),
+                                                                             (lds_u8 *)lds, lnp);
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   conv_ln_reduce<EPI, NW>(lnp, reinterpret_cast<float *>(lds + 2 * Sh::ABYTES), a.ln_part, tid, tid >> 6, lane & 15,
                           lane >> 4);
@@ -404,11 +409,12 @@ const ConvVariant kConvVariants[NRX_CONV_VARIANTS] = {
     {8, 1, 3},            // as 7, workgroups started at staggered times
     {8, 1, 3},            // as 10, workgroups started at staggered times
     {8, 1, 3, 1},         // as 7 on 504-row tiles of whole subcarriers, three 3-tap weight slots
-    {8, 1, 3},            // as 7, wave priority falling through each group (SIMD partners kept level)
+    {8, 1, 3},            // seven 1-tap slots, first fragments of a group loaded before its barrier; tiles of 512,
+                          // 384, 256 or 128 rows, chosen per launch by the number of rows (the default)
 };
 
 template <typename T>
-void launch_conv(const ConvArgs<T> &a, int epi, int variant, int grid, hipStream_t st) {
+void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, hipStream_t st) {
   dim3 blk(256);
 #define NRX_CONV_CASE(V, MBV, OCCV, PF)                                                        \
   if (variant == V) {                                                                         \
@@ -468,9 +474,13 @@ void launch_conv(const ConvArgs<T> &a, int epi, int variant, int grid, hipStream
   NRX_RING_CASE(11, 4, 8, 3, 1, 2, 0, 1, 0)
   NRX_RING_CASE(12, 4, 8, 3, 1, 2, 2, 1, 0)
   NRX_RING_CASE(13, 4, 8, 3, 1, 3, 0, 0, 1)
-  NRX_RING_CASE(14, 4, 8, 3, 1, 2, 3, 0, 0)
+  // the default kernel: tiles of 512 rows, or fewer where the caller's rule says so
+  if (mb == 4) NRX_RING_CASE(14, 4, 8, 3, 1, 7, 4, 0, 0)
+  if (mb == 3) NRX_RING_CASE(14, 3, 8, 3, 1, 7, 4, 0, 0)
+  if (mb == 2) NRX_RING_CASE(14, 2, 8, 3, 1, 7, 4, 0, 0)
+  NRX_RING_CASE(14, 1, 8, 3, 1, 7, 4, 0, 0)
 #undef NRX_RING_CASE
 }
 
-template void launch_conv<float>(const ConvArgs<float> &, int, int, int, hipStream_t);
-template void launch_conv<bf16_t>(const ConvArgs<bf16_t> &, int, int, int, hipStream_t);
+template void launch_conv<float>(const ConvArgs<float> &, int, int, int, int, hipStream_t);
+template void launch_conv<bf16_t>(const ConvArgs<bf16_t> &, int, int, int, int, hipStream_t);

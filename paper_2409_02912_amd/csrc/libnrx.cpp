@@ -59,6 +59,25 @@ constexpr int N_TILE_SIZES = 5;
 constexpr int ALIGNED_TILES = 4;
 inline int tile_size_index(int mb) { return mb / 2 - 1; }
 inline int tile_rows_of_index(int i) { return i == ALIGNED_TILES ? CONV_ALIGNED_TILE : 128 * (i + 1); }
+int num_cu();   // compute units of the current device (256 when it cannot be queried)
+// Tile rows / 128 of the default convolution (1 .. 4) for a launch of so many tiles of 128, 256, 384 and 512
+// rows.  A workgroup fills a CU, so a launch takes ceil(tiles / CUs) rounds, and a round costs about mb + over
+// units: over is what a tile costs beside its MFMAs (pipeline fill, epilogue), 0.8 in BF16 and, the products
+// taking eight times as long, 0.17 in FP32.  Measured on a 128-channel conv, us for mb = 4 / 3 / 2 / 1: 44,352
+// rows 35 / 29 / 23 / 29; 71,232 rows 36 / 30 / 40 / 39; 183,456 rows 72 / 59 / 60 / 74; 366,912 rows
+// 111 / 112 / 116 / 141; 5.9 M rows: 512-row tiles.  The training epilogues that keep or read z hold more than
+// a 512-row tile leaves registers for (max_mb).
+int conv_mb(const std::vector<Tile> *ct, double over, int max_mb) {
+  int best = max_mb;
+  double cost = 1e30;
+  for (int mb = max_mb; mb >= 1; --mb) {
+    const double c = (double)((ct[mb - 1].size() + num_cu() - 1) / num_cu()) * (mb + over);
+    if (c < cost) { cost = c; best = mb; }
+  }
+  return best;
+}
+template <typename T>
+constexpr double conv_over = sizeof(T) == 2 ? 0.8 : 0.17;
 inline int variant_tiles(const ConvVariant &v) { return v.aligned ? ALIGNED_TILES : tile_size_index(v.mb); }
 
 struct TensorInfo {
@@ -167,8 +186,6 @@ std::vector<int64_t> plan_key(const nrx_slot_desc *d, int n, int sim_taps) {
   }
   return k;
 }
-
-int num_cu();   // compute units of the current device (256 when it cannot be queried)
 
 // Validates the descriptors of a batch.  max_ant bounds n_ant, m_max the bits per symbol.
 nrx_status validate_slots(const nrx_slot_desc *d, int n, int max_ant, int m_max) {
@@ -1013,7 +1030,12 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     else if (kConvVariants[v].pref == 2 && ((ca.c0 + ca.c1) / (64 / (int)sizeof(T))) % 2)
       v = 1;   // the LDS-operand kernels walk the input channels two chunks at a time
     const ConvVariant &cv = fp8op ? kConv8Variants[v] : kConvVariants[v];
-    const int ti = variant_tiles(cv);
+    int ti = variant_tiles(cv), mb = 0;
+    if (!fp8op && v == CONV_DEFAULT_VARIANT) {
+      mb = conv_mb(ca.only_m && P->mod_lists ? P->ctm[ca.only_m / 2 - 1] : P->ct, conv_over<T>,
+                   epi == EPI_LN_RELU_SAVE ? 3 : 4);
+      ti = mb - 1;
+    }
     ca.tiles = D.ct[ti];
     ca.n_tiles = (int)P->ct[ti].size();
     if (ca.only_m && P->mod_lists) {   // Var-IO StateInit: only the slots with a UE of this modulation
@@ -1026,7 +1048,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     if constexpr (std::is_same<T, bf16_t>::value) {
       if (fp8op) { launch_conv8(ca, epi, v, grid, st); return; }
     }
-    launch_conv<T>(ca, epi, v, grid, st);
+    launch_conv<T>(ca, epi, v, mb, grid, st);
   };
   auto buf = [&](size_t off) { return (T *)(ws + off); };
   // a bias / LayerNorm vector: the master weights, or its zero-padded copy when d < 128
@@ -1673,17 +1695,19 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
     a.save_stats = const_cast<float *>(stats);
     a.ln_part = lpart;
     a.geo = D.geo;
-    // the LayerNorm-backward epilogue spills in the 8-wave and 2-waves-per-SIMD variants; the one-wave-per-SIMD
-    // LDS-operand variant (384-row tiles) holds it in registers
-    int v = epi == EPI_LN_BWD ? 4 : m->conv_variant[cls];
+    int v = epi == EPI_LN_BWD ? CONV_DEFAULT_VARIANT : m->conv_variant[cls];
     if (kConvVariants[v].pref == 2 && ((a.c0 + a.c1) / (64 / (int)sizeof(T))) % 2) v = 1;
     const ConvVariant &cv = kConvVariants[v];
-    const int ti = variant_tiles(cv);
+    int ti = variant_tiles(cv), mb = 0;
+    if (v == CONV_DEFAULT_VARIANT) {
+      mb = conv_mb(P->ct, conv_over<T>, epi == EPI_LN_BWD ? 3 : 4);
+      ti = mb - 1;
+    }
     a.tiles = D.ct[ti];
     a.n_tiles = (int)P->ct[ti].size();
     int grid = std::min<int>(a.n_tiles, std::min(num_cu() * cv.occ, BWD_GRID_MAX));
     grid = (grid + 7) / 8 * 8;
-    launch_conv<T>(a, epi, v, grid, st);
+    launch_conv<T>(a, epi, v, mb, grid, st);
     return grid;
   };
 
