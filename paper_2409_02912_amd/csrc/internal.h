@@ -239,14 +239,15 @@ struct WgradArgs {
   int n_taps, tap0;         // taps tap0 .. tap0 + n_taps - 1 (dense layers: 1 tap, the centre)
   int n_slices;             // 128-channel input slices
   float *partials;          // [n_part][n_taps * n_slices][128][128]
+  float *bias_part;         // BF16: column sums of dy, [4 n_part][128] (the bias gradient), or null
 };
 template <typename T>
 void launch_wgrad(const WgradArgs<T> &a, hipStream_t st);
 // workgroups launch_wgrad runs per row partition (BF16 3x3 convolutions take three taps per workgroup)
 int wgrad_jobs_per_partition(int n_taps, int n_slices, bool bf16);
 void launch_wgrad_reduce(const float *partials, int n_part, int n_taps, int tap0, int n_slices, int cin_real,
-                         int cin_total, int conv, int64_t dst_off, float *dw, hipStream_t st,
-                         bool acc = false);
+                         int cin_total, int conv, int64_t dst_off, float *dw, hipStream_t st, bool acc,
+                         const float *bias_part, int n_bias, int64_t bias_off);
 template <typename T>
 void launch_colsum(const T *dy, const SlotGeo *geo, int n_slots, float *partial, hipStream_t st);
 void launch_bias_pe(const float *partial, int n_slots, int64_t bias_off, int64_t pe_w_off, int cin_total, int pe_ch,

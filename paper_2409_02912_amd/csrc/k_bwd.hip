@@ -18,29 +18,23 @@
 
 #include "common.h"
 #include "internal.h"
+#include "conv_common.h"
 
 namespace {
 
 constexpr int RS = 64;                  // rows per staging step
 constexpr int TP = RS + 8;              // LDS pitch (elements) of the transposed tiles
 
-// Staging role of a thread: 4 consecutive rows (4*rg ..) x 8 consecutive channels (8*cg ..).
-// Lanes of a wave vary over rg first, so the transposed 4-row LDS stores of one
-// channel from 16 lanes form one contiguous 128-byte run.
-template <typename T>
+// FP32 weight gradient, one tap per workgroup.  Staging role of a thread: 4 consecutive rows (4*rg ..) x 8
+// consecutive channels (8*cg ..).  Lanes of a wave vary over rg first, so the transposed 4-row LDS stores of one
+// channel from 16 lanes form one contiguous run.
 struct WgStage {
   float x[4][8], d[4][8];
 };
-// BF16: the rows as loaded (8 channels = 4 packed words each), half the registers of floats
-template <>
-struct WgStage<bf16_t> {
-  uint32_t x[4][4], d[4][4];
-};
 
-// (the FP32 form's staged rows, twice the BF16 bytes, take most of a CU's LDS: one workgroup per CU, so
-// it asks for one wave per SIMD; the BF16 form for two)
-template <typename T>
-__global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void wgrad_kernel(WgradArgs<T> a) {
+// (the staged rows take most of a CU's LDS: one workgroup per CU, so it asks for one wave per SIMD)
+__global__ __launch_bounds__(256, 1) void wgrad_kernel(WgradArgs<float> a) {
+  using T = float;
   __shared__ __align__(16) T xt[2][128 * TP];
   __shared__ __align__(16) T dt[2][128 * TP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -90,8 +84,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void wgrad_kernel(Wgra
     c.k0 += RS;
     if (c.k0 >= c.nrows) set_tile(c, c.ti + 1);
   };
-  auto load = [&](const Cur &c, WgStage<T> &stg) {
-    stg = WgStage<T>{};
+  auto load = [&](const Cur &c, WgStage &stg) {
+    stg = WgStage{};
     if (c.ti >= t1) return;
     const int rps = 14 * c.U;
 #pragma unroll
@@ -104,49 +98,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void wgrad_kernel(Wgra
         const int sn = s + di, tn = t + dj;
         const bool xin = sn >= 0 && sn < c.S && tn >= 0 && tn < 14 && 8 * cg < cwidth;
         const T *xs = src + (grow + di * rps + dj * c.U) * cs + coff + 8 * cg;
-        if constexpr (sizeof(T) == 2) {
-          const v16 dv = ld16(a.dy + grow * NRX_D + 8 * cg);
-#pragma unroll
-          for (int w = 0; w < 4; ++w) stg.d[q][w] = dv.w[w];
-          if (xin) {
-            const v16 xv = ld16(xs);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) stg.x[q][w] = xv.w[w];
-          }
-        } else {
-          pack8<T>::load(a.dy + grow * NRX_D + 8 * cg, stg.d[q]);
-          if (xin) pack8<T>::load(xs, stg.x[q]);
-        }
+        pack8<T>::load(a.dy + grow * NRX_D + 8 * cg, stg.d[q]);
+        if (xin) pack8<T>::load(xs, stg.x[q]);
       }
     }
   };
-  auto store = [&](int b, const WgStage<T> &stg) {
-    if constexpr (sizeof(T) == 2) {
-      // channel 2w / 2w + 1 of rows (q, q + 1) from the low / high halves of word w: the 4 rows of a channel
-      // are contiguous in the transposed tile, one 8-byte store per channel and array
+  auto store = [&](int b, const WgStage &stg) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t xl[2], xh[2], dl[2], dh[2];
+    for (int e = 0; e < 8; ++e) {
+      T *xp = &xt[b][(8 * cg + e) * TP + 4 * rg];
+      T *dp = &dt[b][(8 * cg + e) * TP + 4 * rg];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          xl[p] = (stg.x[2 * p][w] & 0xFFFFu) | (stg.x[2 * p + 1][w] << 16);
-          xh[p] = (stg.x[2 * p][w] >> 16) | (stg.x[2 * p + 1][w] & 0xFFFF0000u);
-          dl[p] = (stg.d[2 * p][w] & 0xFFFFu) | (stg.d[2 * p + 1][w] << 16);
-          dh[p] = (stg.d[2 * p][w] >> 16) | (stg.d[2 * p + 1][w] & 0xFFFF0000u);
-        }
-        *reinterpret_cast<uint2 *>(&xt[b][(8 * cg + 2 * w) * TP + 4 * rg]) = make_uint2(xl[0], xl[1]);
-        *reinterpret_cast<uint2 *>(&xt[b][(8 * cg + 2 * w + 1) * TP + 4 * rg]) = make_uint2(xh[0], xh[1]);
-        *reinterpret_cast<uint2 *>(&dt[b][(8 * cg + 2 * w) * TP + 4 * rg]) = make_uint2(dl[0], dl[1]);
-        *reinterpret_cast<uint2 *>(&dt[b][(8 * cg + 2 * w + 1) * TP + 4 * rg]) = make_uint2(dh[0], dh[1]);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        T *xp = &xt[b][(8 * cg + e) * TP + 4 * rg];
-        T *dp = &dt[b][(8 * cg + e) * TP + 4 * rg];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { xp[q] = elem<T>::from_f(stg.x[q][e]); dp[q] = elem<T>::from_f(stg.d[q][e]); }
-      }
+      for (int q = 0; q < 4; ++q) { xp[q] = elem<T>::from_f(stg.x[q][e]); dp[q] = elem<T>::from_f(stg.d[q][e]); }
     }
   };
 
@@ -158,7 +121,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void wgrad_kernel(Wgra
     next(c1);
     c2 = c1;
     if (c2.ti < t1) next(c2);
-    WgStage<T> s0, s1;
+    WgStage s0, s1;
     load(c0, s0);
     store(0, s0);
     load(c1, s1);
@@ -199,41 +162,84 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void wgrad_kernel(Wgra
         dst[((4 * wm + m) * 16 + 4 * lk + i) * 128 + (4 * wn + n) * 16 + lr] = acc[m][n][i];
 }
 
-// BF16 weight gradient of a 3x3 convolution, three taps per workgroup.  A workgroup owns one (row
-// partition, tap row di, 128-channel input slice) and the three taps dj = -1, 0, 1 of that row: per
-// 64-row step it stages dY once (transposed) and the three dj-shifted input windows (transposed, rows
-// whose neighbour lies outside the grid zero), so every staged dY row feeds three 128x128 blocks.  Eight
-// waves: 4 (32 input channels) x 2 (64 output channels), each holding 3 x 2 x 4 MFMA blocks.  The
-// partials go to the same [partition][tap][slice] layout as wgrad_kernel, summed by the same reduce.
-constexpr int W3_WAVES = 8;
+// BF16 weight gradient: NT = 3 taps of one tap row (3x3 convolutions), or the one tap of a dense layer, per
+// workgroup.  The contraction runs over rows, but rows are what memory keeps apart: both operands have their K
+// index outside.  They go to LDS as they lie in memory, by DMA, and ds_read_b64_tr_b16 transposes on the way to
+// the registers (four rows of 16 channels per 16 lanes), so no lane packs or shuffles anything; the kernel
+// before this one loaded rows to registers, repacked them and stored them transposed, at 17 % of the MFMA rate.
+//
+// A step is 64 rows: dY once, and of the input the window of rows that the NT taps dj share (U rows more on
+// either side); a tap reads it dj U rows further.  A row whose neighbour lies outside the grid in t reads a zero
+// row instead, in s the DMA reads zeros.  LDS rows are 256 bytes, 32-byte pieces XOR-swizzled by the row: the 16
+// lanes of a transposed read take four rows, which then lie on distinct banks.  Eight waves: 4 (32 input
+// channels) x 2 (64 output channels), NT x 2 x 4 MFMA blocks each.
+//
+// Four step buffers: while step k computes, k + 1 has landed (its first fragments are read in the last part of
+// step k and carried over the barrier), k + 2 and k + 3 are on their way.  Every wave issues the same number of
+// copies per step, so the wait counts copies and leaves the last step's in flight.
+//
+// The workgroups of one row partition (3 tap rows, or more with two input slices) are consecutive on one XCD
+// and move in step: the partition's rows come from memory once and from that XCD's L2 after that.
+//
+// The column sums of dY (bias gradients) fall out of the same fragments: one more product with a row of ones,
+// each of the four waves that hold the same columns taking every fourth K block.
+//
+// 64 slots x 106 PRB x 4 UEs (4.6 M rows), 128 -> 128 channels: 3.1 -> 1.75 ms (0.77 PFLOP/s), and the pass of its
+// own for the column sums (0.48 ms) is gone; 32 slots x 8 PRB: 127 -> 74 us.  A dense layer: 0.44 -> 0.41 ms, the
+// 2.3 GB of its operands at 5.7 TB/s.  The fragment reads (104 of 128 bytes a clock at the full MFMA rate) bound it.
+namespace wtr {
+constexpr int STEP = 64;                       // rows per step
+constexpr int RB = 2 * NRX_D;                // bytes per LDS row
+constexpr int NBUF = 4;
+template <int NT>
+struct Shape {
+  static constexpr int XROWS = STEP + (NT == 3 ? 2 * NRX_MAXU : 0);    // input window of the taps
+  static constexpr int XINS = XROWS / 4, DINS = STEP / 4;              // copies of 1 KB: four rows
+  static constexpr int COPIES = (XINS + DINS + 7) / 8;                 // per wave and step
+  static constexpr int BUFB = (XROWS + STEP) * RB;
+  static constexpr int ZERO = NBUF * BUFB;     // 1 KB of zeros: rows outside the grid, and where spare copies go
+  static constexpr int LDS_BYTES = ZERO + 1024;
+};
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+__device__ __forceinline__ uint2 read_tr(uint32_t addr) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)(uintptr_t)addr));
+}
+}  // namespace wtr
 
-__global__ __launch_bounds__(64 * W3_WAVES, 1) void wgrad3_kernel(WgradArgs<bf16_t> a) {
-  __shared__ __align__(16) bf16_t xt[2][3][128 * TP];
-  __shared__ __align__(16) bf16_t dt[2][128 * TP];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int NT>
+__global__ __launch_bounds__(512, 1) void wgrad_tr_kernel(WgradArgs<bf16_t> a) {
+  using namespace wtr;
+  using Sh = Shape<NT>;
+  constexpr int XROWS = Sh::XROWS, XINS = Sh::XINS, DINS = Sh::DINS, COPIES = Sh::COPIES, BUFB = Sh::BUFB, ZERO = Sh::ZERO;
+  static_assert(COPIES < 16, "vmcnt immediate below");
+  __shared__ __align__(1024) unsigned char lds_raw[Sh::LDS_BYTES];
+  const uint32_t lds = lds_addr((lds_u8 *)lds_raw);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;   // 32 input channels x 64 output channels per wave
-  constexpr int KF = mma<bf16_t>::KF;
-  const int njob = 3 * a.n_slices;
-  const int part = blockIdx.x / njob, job = blockIdx.x % njob;
-  const int dg = job / a.n_slices, slice = job % a.n_slices;
+  // XCD-aware order (workgroups go round-robin over the 8 XCDs): consecutive indexes share an XCD
+  const int njob = (NT == 3 ? 3 : 1) * a.n_slices;
+  const int nx = (gridDim.x + 7) >> 3;
+  const int idx = (blockIdx.x & 7) * nx + (blockIdx.x >> 3);
+  if (idx >= a.n_part * njob) return;
+  const int part = idx / njob, job = idx - part * njob;
+  const int dg = NT == 3 ? job / a.n_slices : 1, slice = NT == 3 ? job - dg * a.n_slices : job;
   const int di = dg - 1;
   const bf16_t *src;
   int cs, coff;
   if (slice * 128 < a.c0) { src = a.src0; cs = a.c0; coff = slice * 128; }
   else { src = a.src1; cs = a.c1; coff = slice * 128 - a.c0; }
   const int cwidth = cs - coff < 128 ? cs - coff : 128;
+  const bool live = 32 * wm < cwidth;        // a wave whose input channels do not exist only copies and sums
+  const bool sums = a.bias_part && di == 0 && slice == 0;
 
-  f32x4_t acc[3][2][4];
-#pragma unroll
-  for (int t = 0; t < 3; ++t)
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 4; ++n) acc[t][m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int e = tid; e < 1024 / 16; e += 512) st16((lds_u8 *)lds_raw + ZERO + 16 * e, v16{{0, 0, 0, 0}});
 
   const int t0 = (int)((int64_t)a.n_tiles * part / a.n_part);
   const int t1 = (int)((int64_t)a.n_tiles * (part + 1) / a.n_part);
+  // cursor over the steps of the partition (wave-uniform)
   struct Cur {
     int ti, k0, nrows, row0, U, S;
     int64_t base;
@@ -242,8 +248,8 @@ __global__ __launch_bounds__(64 * W3_WAVES, 1) void wgrad3_kernel(WgradArgs<bf16
     c.ti = ti;
     c.k0 = 0;
     if (ti < t1) {
-      const Tile tl = a.tiles[ti];
-      const SlotGeo &g = a.geo[tl.slot];
+      const Tile tl = ldc(a.tiles + ti);
+      const SlotGeo g = ldc_geo(a.geo + tl.slot);
       c.nrows = tl.nrows;
       c.row0 = tl.row0;
       c.U = g.U;
@@ -252,111 +258,151 @@ __global__ __launch_bounds__(64 * W3_WAVES, 1) void wgrad3_kernel(WgradArgs<bf16
     }
   };
   auto next = [&](Cur &c) {
-    c.k0 += RS;
+    if (c.ti >= t1) return;
+    c.k0 += STEP;
     if (c.k0 >= c.nrows) set_tile(c, c.ti + 1);
   };
-  // staging pairs of a thread: p = tid + 512 j; which = p / 256 (0..2: input window of tap dj = which - 1,
-  // 3: dY); 4 consecutive rows (4 rg ..) x 8 consecutive channels (8 cg ..) of the step
-  struct Stage {
-    uint32_t v[2][4][4];
-  };
-  auto load = [&](const Cur &c, Stage &stg) {
+  // this lane's part of a copy: row (lane / 16) of four, 16-byte piece lane % 16, swizzled in pairs
+  auto issue = [&](const Cur &c, int b) {
+    const bool on = c.ti < t1;
+    const int rps = 14 * c.U, wrows = STEP + (NT == 3 ? 2 * c.U : 0);
+    const i32x4_t xrs = on ? rsrc_words(src + c.base * cs + coff, c.S * rps * cs * 2) : rsrc_words(src, 0);
+    const i32x4_t drs = on ? rsrc_words(a.dy + (c.base + c.row0) * NRX_D, c.nrows * RB) : rsrc_words(a.dy, 0);
+    const uint32_t buf = lds + b * BUFB;
+    const int xrow0 = c.row0 + c.k0 + di * rps - (NT == 3 ? c.U : 0);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int p = tid + 512 * j, which = p >> 8, q = p & 255, rg = q & 15, cg = q >> 4;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) stg.v[j][r4][w] = 0u;
-      if (c.ti >= t1) continue;
-      const int rps = 14 * c.U;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int r = c.k0 + 4 * rg + r4;
-        if (r >= c.nrows) continue;
-        const int R = c.row0 + r;
-        const int64_t grow = c.base + R;
-        if (which == 3) {
-          const v16 dv = ld16(a.dy + grow * NRX_D + 8 * cg);
-#pragma unroll
-          for (int w = 0; w < 4; ++w) stg.v[j][r4][w] = dv.w[w];
-        } else {
-          const int dj = which - 1;
-          const int s = R / rps, t = (R - s * rps) / c.U;
-          const int sn = s + di, tn = t + dj;
-          if (sn >= 0 && sn < c.S && tn >= 0 && tn < 14 && 8 * cg < cwidth) {
-            const v16 xv = ld16(src + (grow + di * rps + dj * c.U) * cs + coff + 8 * cg);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) stg.v[j][r4][w] = xv.w[w];
-          }
-        }
-      }
-    }
-  };
-  auto store = [&](int b, const Stage &stg) {
-    // channel 2w / 2w + 1 of rows (q, q + 1) from the low / high halves of word w: the 4 rows of a channel are
-    // contiguous in the transposed tile, one 8-byte store per channel
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int p = tid + 512 * j, which = p >> 8, q = p & 255, rg = q & 15, cg = q >> 4;
-      bf16_t *dst = which == 3 ? dt[b] : xt[b][which];
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t lo[2], hi[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          lo[h] = (stg.v[j][2 * h][w] & 0xFFFFu) | (stg.v[j][2 * h + 1][w] << 16);
-          hi[h] = (stg.v[j][2 * h][w] >> 16) | (stg.v[j][2 * h + 1][w] & 0xFFFF0000u);
-        }
-        *reinterpret_cast<uint2 *>(&dst[(8 * cg + 2 * w) * TP + 4 * rg]) = make_uint2(lo[0], lo[1]);
-        *reinterpret_cast<uint2 *>(&dst[(8 * cg + 2 * w + 1) * TP + 4 * rg]) = make_uint2(hi[0], hi[1]);
-      }
+    for (int j = 0; j < COPIES; ++j) {
+      const int ins = wave + 8 * j;
+      const bool isd = ins >= XINS, spare = ins >= XINS + DINS;
+      const int row = 4 * (isd ? ins - XINS : ins) + (lane >> 4);   // row of the window or of dY
+      const int p = lane & 15, piece = (((p >> 1) ^ (row & 7)) << 1) | (p & 1);
+      uint32_t voff;
+      if (isd) voff = (uint32_t)((c.k0 + row) * RB + piece * 16);
+      else voff = row < wrows && piece * 8 < cwidth ? (uint32_t)((xrow0 + row) * cs * 2 + piece * 16) : 0x80000000u;
+      if (!on || spare) voff = 0x80000000u;
+      const uint32_t dst = spare || !on ? lds + ZERO : buf + (isd ? XROWS * RB + (ins - XINS) * 1024 : ins * 1024);
+      dma16(isd ? drs : xrs, __builtin_amdgcn_readfirstlane(dst), voff);
     }
   };
 
-  // pipeline: LDS buffer b holds step k; registers hold steps k+1 (s1) and k+2 (being loaded into s0)
-  Cur c0, c1, c2;
+  f32x4_t acc[NT][2][4], bsum[4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) acc[t][m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int n = 0; n < 4; ++n) bsum[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const uint32_t one2 = 0x3F803F80u;
+  const v16 ones = {{one2, one2, one2, one2}};
+
+  const int rr = lr >> 2, c8 = 8 * (lr & 3);   // row of four and 8-byte chunk a lane points at
+  // dY addresses within a buffer: K rows 8 lk + 4 h + rr of a 32-row block, n-block n at ^ (n << 5)
+  uint32_t db[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = 8 * lk + 4 * h + rr;
+    db[h] = (uint32_t)(XROWS * RB + r * RB + (((4 * wn) ^ (r & 7)) << 5) + c8);
+  }
+  // input addresses of a step: [tap][ks][h], m-block m at ^ (m << 5)
+  uint32_t xa[NT][2][2];
+  auto addresses = [&](const Cur &c, int b) {
+    const uint32_t buf = lds + b * BUFB;
+    const int U = c.U, rps = 14 * U;
+    const float inv = 1.0f / (float)rps;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = 32 * ks + 8 * lk + 4 * h + rr;
+        const int R = c.row0 + c.k0 + r;
+        // row within its subcarrier: the quotient is below 2^14 and at least 0.5 / rps from an integer
+        const int rem = R - (int)(((float)R + 0.5f) * inv) * rps;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int xr = r + (NT == 3 ? t * U : 0);
+          const bool out = NT == 3 && ((t == 0 && rem < U) || (t == 2 && rem >= 13 * U));
+          xa[t][ks][h] = out ? lds + ZERO + c8 : buf + xr * RB + (((2 * wm) ^ (xr & 7)) << 5) + c8;
+        }
+      }
+  };
+  auto load_x = [&](int t, int ks, v16 (&f)[2]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const uint2 lo = read_tr(xa[t][ks][0] ^ (m << 5)), hi = read_tr(xa[t][ks][1] ^ (m << 5));
+      f[m] = v16{{lo.x, lo.y, hi.x, hi.y}};
+    }
+  };
+  auto load_d = [&](uint32_t buf, int ks, int n) {
+    const uint2 lo = read_tr(buf + ks * 32 * RB + (db[0] ^ (n << 5)));
+    const uint2 hi = read_tr(buf + ks * 32 * RB + (db[1] ^ (n << 5)));
+    return v16{{lo.x, lo.y, hi.x, hi.y}};
+  };
+
+  Cur c0, ci;
   set_tile(c0, t0);
   if (c0.ti < t1) {
-    c1 = c0;
-    next(c1);
-    c2 = c1;
-    if (c2.ti < t1) next(c2);
-    Stage s0, s1;
-    load(c0, s0);
-    store(0, s0);
-    load(c1, s1);
-    __syncthreads();
-    int b = 0;
+    ci = c0;
+#pragma unroll 1
+    for (int j = 0; j < NBUF - 1; ++j) { issue(ci, j); next(ci); }
+    __builtin_amdgcn_s_waitcnt(0x0070 | 0x0F00 | COPIES);   // the first two steps have landed
+    __syncthreads();                                        // (and the zero row is written)
+    int b = 0, step = 0;
+    v16 xf[2], xn[2], df[4], dn[4];
+    addresses(c0, 0);
+    load_x(0, 0, xf);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) df[n] = load_d(lds, 0, n);
     while (c0.ti < t1) {
-      load(c2, s0);
+      issue(ci, (b + NBUF - 1) % NBUF);
+      next(ci);
+      const uint32_t buf = lds + b * BUFB, bufn = lds + ((b + 1) % NBUF) * BUFB;
+      Cur cn = c0;
+      next(cn);
 #pragma unroll
-      for (int f = 0; f < RS / KF; ++f) {
-        v16 bfr[4];
+      for (int i = 0; i < 2 * NT; ++i) {
+        const int ks = i / NT, t = i % NT;
+        // the next products' fragments: the input of the next tap, and of dY a share of the next K block
+        if (i + 1 < 2 * NT) load_x((i + 1) % NT, (i + 1) / NT, xn);
+        else {
+          if (cn.ti < t1) addresses(cn, (b + 1) % NBUF);
+          load_x(0, 0, xn);
+        }
 #pragma unroll
-        for (int n = 0; n < 4; ++n) bfr[n] = ld16(&dt[b][((4 * wn + n) * 16 + lr) * TP + f * KF + lk * (KF / 4)]);
+        for (int n = 0; n < 4; ++n)
+          if (n * NT / 4 == t) dn[n] = ks == 0 ? load_d(buf, 1, n) : load_d(bufn, 0, n);
+        if (live) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+          for (int m = 0; m < 2; ++m)
 #pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            const v16 af = ld16(&xt[b][t][((2 * wm + m) * 16 + lr) * TP + f * KF + lk * (KF / 4)]);
+            for (int n = 0; n < 4; ++n) acc[t][m][n] = mfma_bf16(xf[m], df[n], acc[t][m][n]);
+        }
+        if (t == NT - 1) {
+          if (sums && wm == 2 * (step & 1) + ks) {
 #pragma unroll
-            for (int n = 0; n < 4; ++n) acc[t][m][n] = mfma_bf16(af, bfr[n], acc[t][m][n]);
+            for (int n = 0; n < 4; ++n) bsum[n] = mfma_bf16(ones, df[n], bsum[n]);
           }
-      }
-      if (c1.ti < t1) store(b ^ 1, s1);
-      __syncthreads();
-      b ^= 1;
-      c0 = c1;
-      c1 = c2;
-      if (c2.ti < t1) next(c2);
-      s1 = s0;
-    }
-  }
-  // partials [part][tap][slice][c 128][o 128], tap = 3 (di + 1) + (dj + 1)
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    float *dst = a.partials + ((int64_t)part * 9 * a.n_slices + (3 * dg + t) * a.n_slices + slice) * 128 * 128;
+          for (int n = 0; n < 4; ++n) df[n] = dn[n];
+        }
+        xf[0] = xn[0];
+        xf[1] = xn[1];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_waitcnt(0x0070 | 0x0F00 | COPIES);   // step k + 2 has landed, k + 3 may be on its way
+      dma_barrier();
+      c0 = cn;
+      b = (b + 1) % NBUF;
+      ++step;
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // no copy into LDS outlives the loop
+  }
+  // partials [part][tap][slice][c 128][o 128]; D layout: lane holds c = 4 lk + i, o = lr (per block)
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int tap = NT == 3 ? 3 * dg + t : 0;
+    float *dst = a.partials + (((int64_t)part * (NT == 3 ? 9 : 1) + tap) * a.n_slices + slice) * 128 * 128;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -365,20 +411,49 @@ __global__ __launch_bounds__(64 * W3_WAVES, 1) void wgrad3_kernel(WgradArgs<bf16
         for (int i = 0; i < 4; ++i)
           dst[((2 * wm + m) * 16 + 4 * lk + i) * 128 + (4 * wn + n) * 16 + lr] = acc[t][m][n][i];
   }
+  if (sums && lk == 0) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) a.bias_part[((int64_t)part * 4 + wm) * 128 + (4 * wn + n) * 16 + lr] = bsum[n][0];
+  }
 }
 
-// dw[layout] = sum over partitions, fixed order (added to dw when acc)
-__global__ void wgrad_reduce_kernel(const float *partials, int n_part, int n_taps, int tap0, int n_slices,
-                                    int cin_real, int cin_total, int conv, int64_t dst_off, float *dw, int acc) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// sum of n values p[0], p[stride], .. in fp64, in that order; the loads go out sixteen at a time (added up one by
+// one a sum was a chain of memory latencies, 55 us for 85 partitions)
+__device__ __forceinline__ double sum_strided(const float *p, int n, int64_t stride) {
+  double s = 0.0;
+  int k = 0;
+  for (; k + 16 <= n; k += 16) {
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = p[(int64_t)(k + i) * stride];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += v[i];
+  }
+  for (; k < n; ++k) s += p[(int64_t)k * stride];
+  return s;
+}
+
+// dw[layout] = sum over partitions, fixed order (added to dw when acc); the last block adds up the bias gradient
+// [n_bias][128] where there is one
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *partials, int n_part, int n_taps, int tap0,
+                                                           int n_slices, int cin_real, int cin_total, int conv,
+                                                           int64_t dst_off, float *dw, int acc, const float *bias_part,
+                                                           int n_bias, int64_t bias_off) {
   const int njob = n_taps * n_slices;
-  if (e >= (int64_t)njob * 128 * 128) return;
+  if (blockIdx.x == njob * 128 * 128 / 256) {
+    if (threadIdx.x < 128) {
+      const double s = sum_strided(bias_part + threadIdx.x, n_bias, 128);
+      float *d = dw + bias_off + threadIdx.x;
+      *d = acc ? *d + (float)s : (float)s;
+    }
+    return;
+  }
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int o = e % 128, c = (e / 128) % 128, job = e / (128 * 128);
   const int tap = tap0 + job / n_slices, slice = job % n_slices;
   const int cg = slice * 128 + c;
   if (cg >= cin_real) return;
-  double s = 0.0;
-  for (int p = 0; p < n_part; ++p) s += partials[((int64_t)p * njob + job) * 128 * 128 + c * 128 + o];
+  const double s = sum_strided(partials + e, n_part, (int64_t)njob * 128 * 128);
   const int64_t idx = conv ? ((int64_t)tap * cin_total + cg) * 128 + o : (int64_t)cg * 128 + o;
   dw[dst_off + idx] = acc ? dw[dst_off + idx] + (float)s : (float)s;
 }
@@ -481,13 +556,30 @@ __global__ void bias_pe_kernel(const float *red, int64_t bias_off, int64_t pe_w_
   dw[w + 128] = (float)gf;
 }
 
+// Column sums of part[n][width] in fp64, 32 columns per workgroup: eight threads of a column add up every eighth
+// row, then one adds the eight.  (One thread per column, in one workgroup, took 60 us for 256 rows and 400 us for
+// the 1024 x 1032 readout partials.)  out(column, sum) stores.
+template <typename Out>
+__device__ __forceinline__ void column_sums(const float *part, int n, int width, Out out) {
+  __shared__ double red[8][32];
+  const int col = threadIdx.x & 31, k = threadIdx.x >> 5, c = blockIdx.x * 32 + col;
+  red[k][col] = c < width && k < n ? sum_strided(part + (int64_t)k * width + c, (n - k + 7) / 8, 8LL * width) : 0.0;
+  __syncthreads();
+  if (k == 0 && c < width) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += red[i][col];
+    out(c, s);
+  }
+}
+
 // LayerNorm parameter gradients from per-workgroup partials [n][256].
-__global__ void ln_reduce_kernel(const float *part, int n, int64_t g_off, int64_t b_off, float *dw) {
-  const int c = threadIdx.x;   // 0..255
-  double s = 0.0;
-  for (int k = 0; k < n; ++k) s += part[(int64_t)k * 256 + c];
-  if (c < 128) dw[g_off + c] = (float)s;
-  else dw[b_off + c - 128] = (float)s;
+__global__ __launch_bounds__(256) void ln_reduce_kernel(const float *part, int n, int64_t g_off, int64_t b_off,
+                                                        float *dw) {
+  column_sums(part, n, 256, [&](int c, double s) {
+    if (c < 128) dw[g_off + c] = (float)s;
+    else dw[b_off + c - 128] = (float)s;
+  });
 }
 
 // --------------------------------------------------------------- MP / readout
@@ -780,18 +872,16 @@ __global__ void select_rows_kernel(const T *src, const SlotGeo *geo, int only_m,
   pack8<T>::store(dst + o, v);
 }
 
-__global__ void readout_w2_reduce_kernel(const float *part, int n, int m_max, int64_t w2_off, int64_t b2_off,
-                                         float *dw, int j0) {
-  const int e = threadIdx.x + blockIdx.x * blockDim.x;   // 0..1031
-  if (e >= 1032) return;
-  double s = 0.0;
-  for (int k = 0; k < n; ++k) s += part[(int64_t)k * 1032 + e];
-  if (e < 1024) {
-    const int c = e / 8, j = j0 + e % 8;
-    if (j < m_max) dw[w2_off + c * m_max + j] = (float)s;
-  } else if (j0 + e - 1024 < m_max) {
-    dw[b2_off + j0 + e - 1024] = (float)s;
-  }
+__global__ __launch_bounds__(256) void readout_w2_reduce_kernel(const float *part, int n, int m_max, int64_t w2_off,
+                                                                int64_t b2_off, float *dw, int j0) {
+  column_sums(part, n, 1032, [&](int e, double s) {
+    if (e < 1024) {
+      const int c = e / 8, j = j0 + e % 8;
+      if (j < m_max) dw[w2_off + c * m_max + j] = (float)s;
+    } else if (j0 + e - 1024 < m_max) {
+      dw[b2_off + j0 + e - 1024] = (float)s;
+    }
+  });
 }
 
 }  // namespace
@@ -799,22 +889,23 @@ __global__ void readout_w2_reduce_kernel(const float *part, int n, int m_max, in
 template <typename T>
 void launch_wgrad(const WgradArgs<T> &a, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
-    if (a.n_taps == 9) {   // 3x3 convolutions: three taps per workgroup
-      hipLaunchKernelGGL(wgrad3_kernel, dim3(a.n_part * 3 * a.n_slices), dim3(64 * W3_WAVES), 0, st, a);
-      return;
-    }
+    const int n = a.n_part * wgrad_jobs_per_partition(a.n_taps, a.n_slices, true);
+    const dim3 grid((n + 7) / 8 * 8);   // whole XCD rounds; the spare workgroups return at once
+    if (a.n_taps == 9) hipLaunchKernelGGL(wgrad_tr_kernel<3>, grid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL(wgrad_tr_kernel<1>, grid, dim3(512), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(wgrad_kernel, dim3(a.n_part * a.n_taps * a.n_slices), dim3(256), 0, st, a);
   }
-  const int grid = a.n_part * a.n_taps * a.n_slices;
-  hipLaunchKernelGGL(wgrad_kernel<T>, dim3(grid), dim3(256), 0, st, a);
 }
 int wgrad_jobs_per_partition(int n_taps, int n_slices, bool bf16) {
   return (bf16 && n_taps == 9) ? 3 * n_slices : n_taps * n_slices;
 }
 void launch_wgrad_reduce(const float *partials, int n_part, int n_taps, int tap0, int n_slices, int cin_real,
-                         int cin_total, int conv, int64_t dst_off, float *dw, hipStream_t st, bool acc) {
-  const int64_t n = (int64_t)n_taps * n_slices * 128 * 128;
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, partials, n_part,
-                     n_taps, tap0, n_slices, cin_real, cin_total, conv, dst_off, dw, acc ? 1 : 0);
+                         int cin_total, int conv, int64_t dst_off, float *dw, hipStream_t st, bool acc,
+                         const float *bias_part, int n_bias, int64_t bias_off) {
+  const int blocks = n_taps * n_slices * 128 * 128 / 256 + (bias_part ? 1 : 0);
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks), dim3(256), 0, st, partials, n_part, n_taps, tap0, n_slices,
+                     cin_real, cin_total, conv, dst_off, dw, acc ? 1 : 0, bias_part, n_bias, bias_off);
 }
 template <typename T>
 void launch_colsum(const T *dy, const SlotGeo *geo, int n_slots, float *partial, hipStream_t st) {
@@ -829,7 +920,7 @@ void launch_bias_pe(const float *partial, int n_slots, int64_t bias_off, int64_t
                      pe_ch, dw, acc ? 1 : 0);
 }
 void launch_ln_reduce(const float *part, int n, int64_t g_off, int64_t b_off, float *dw, hipStream_t st) {
-  hipLaunchKernelGGL(ln_reduce_kernel, dim3(1), dim3(256), 0, st, part, n, g_off, b_off, dw);
+  hipLaunchKernelGGL(ln_reduce_kernel, dim3(8), dim3(256), 0, st, part, n, g_off, b_off, dw);
 }
 template <typename T>
 void launch_mp_bwd(const MpBwdArgs<T> &a, int grid, hipStream_t st) {
@@ -850,7 +941,7 @@ void launch_readout_bwd(const RoBwdArgs<T> &a, int grid, hipStream_t st) {
 }
 void launch_readout_w2_reduce(const float *part, int n, int m_max, int64_t w2_off, int64_t b2_off, float *dw,
                               hipStream_t st, int j0) {
-  hipLaunchKernelGGL(readout_w2_reduce_kernel, dim3(5), dim3(256), 0, st, part, n, m_max, w2_off, b2_off, dw, j0);
+  hipLaunchKernelGGL(readout_w2_reduce_kernel, dim3(33), dim3(256), 0, st, part, n, m_max, w2_off, b2_off, dw, j0);
 }
 
 template void launch_wgrad<float>(const WgradArgs<float> &, hipStream_t);

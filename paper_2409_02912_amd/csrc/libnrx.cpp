@@ -803,7 +803,7 @@ struct FwdLayout {
   std::vector<size_t> q_ch;   // the same for ReadoutChEst
   // backward (training layout only)
   size_t bjobs = 0, bprep = 0, zero = 0, dh = 0, dz = 0, dagg = 0, dmsg = 0, dm1 = 0, dr = 0;
-  size_t wpart = 0, cpart = 0, lpart = 0, rpart = 0;
+  size_t wpart = 0, bpart = 0, cpart = 0, lpart = 0, rpart = 0;
   size_t total;
 };
 
@@ -870,6 +870,7 @@ FwdLayout fwd_layout(const nrx_model *m, const Plan *P, bool save) {
     // partitions x (taps x slices) 128x128 partial blocks: <= 2 per CU for the one-tap-per-workgroup kernel,
     // <= 3 per CU for the three-tap kernel (one workgroup per CU)
     L.wpart = o; o = align256(o + (size_t)3 * num_cu() * 128 * 128 * 4);
+    L.bpart = o; o = align256(o + (size_t)4 * WGRAD_PARTS * 128 * 4);   // bias gradients of the partitions
     L.cpart = o; o = align256(o + (size_t)(P->n + 1) * 14 * 768 * 4);   // per-slot partials + reduced table
     L.lpart = o; o = align256(o + (size_t)BWD_GRID_MAX * 256 * 4);
     // dW2 partials: one set per readout for ReadoutLLRs, two (column groups) for ReadoutChEst
@@ -1651,14 +1652,17 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
   HIPCHK(hipMemsetAsync(ws + L.zero, 0, 128 * 4, st));
   auto buf = [&](size_t off) { return (T *)(ws + off); };
   const float *zero = (const float *)(ws + L.zero);
-  float *wpart = (float *)(ws + L.wpart), *cpart = (float *)(ws + L.cpart);
+  float *wpart = (float *)(ws + L.wpart), *bpart = (float *)(ws + L.bpart), *cpart = (float *)(ws + L.cpart);
   float *lpart = (float *)(ws + L.lpart), *rpart = (float *)(ws + L.rpart);
   const int d = NRX_D;
   const int ti256 = tile_size_index(4);
   const int grid_mlp = std::min<int>((int)std::max(P->mt.size(), P->rt.size()), std::min(num_cu() * 4, BWD_GRID_MAX));
 
+  // weight gradient of a layer, and its bias gradient: from the same pass over dY in BF16; in FP32, and where the
+  // layer folds positional-encoding channels into a table (pe_w_off), from column sums per table entry
   auto wgrad = [&](const T *src0, int c0, const T *src1, int c1, const T *dy, bool conv, int cin_real, int cin_total,
-                   int64_t dst, bool acc = false) {
+                   int64_t dst, int64_t bias_off, int64_t pe_w_off = -1, int pe_ch = 0, bool acc = false) {
+    constexpr bool bf16 = std::is_same<T, bf16_t>::value;
     WgradArgs<T> a{};
     a.src0 = src0; a.c0 = c0; a.src1 = src1; a.c1 = c1;
     a.dy = dy;
@@ -1668,18 +1672,19 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
     a.n_taps = conv ? 9 : 1;
     a.tap0 = conv ? 0 : 4;
     a.n_slices = (c0 + c1 + 127) / 128;
-    // one round of workgroups (2 per CU; 1 for the 8-wave three-tap kernel), all with the same number of rows
-    const int jobs = wgrad_jobs_per_partition(a.n_taps, a.n_slices, std::is_same<T, bf16_t>::value);
-    const int per_cu = jobs == a.n_taps * a.n_slices ? 2 : 1;
-    a.n_part = std::max(1, std::min(WGRAD_PARTS, (per_cu * num_cu()) / jobs));
+    // one round of workgroups (2 per CU; 1 for the 8-wave BF16 kernel), all with the same number of rows
+    const int jobs = wgrad_jobs_per_partition(a.n_taps, a.n_slices, bf16);
+    a.n_part = std::max(1, std::min(WGRAD_PARTS, ((bf16 ? 1 : 2) * num_cu()) / jobs));
     a.partials = wpart;
+    const bool fused = bf16 && pe_w_off < 0;
+    a.bias_part = fused ? bpart : nullptr;
     launch_wgrad<T>(a, st);
     launch_wgrad_reduce(wpart, a.n_part, a.n_taps, a.tap0, a.n_slices, cin_real, cin_total, conv ? 1 : 0, dst, dw,
-                        st, acc);
-  };
-  auto bias = [&](const T *dy, int64_t bias_off, int64_t pe_w_off, int cin_total, int pe_ch, bool acc = false) {
-    launch_colsum<T>(dy, D.geo, P->n, cpart, st);
-    launch_bias_pe(cpart, P->n, bias_off, pe_w_off, cin_total, pe_ch, dw, st, acc);
+                        st, acc, a.bias_part, 4 * a.n_part, bias_off);
+    if (!fused) {
+      launch_colsum<T>(dy, D.geo, P->n, cpart, st);
+      launch_bias_pe(cpart, P->n, bias_off, pe_w_off, cin_total, pe_ch, dw, st, acc);
+    }
   };
   auto dgrad = [&](const T *src, const T *wt, int epi, int cls, T *out, const T *resid, const T *z, const float *stats,
                    const float *g) {
@@ -1754,8 +1759,7 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
       a.tiles = D.rt;
       a.n_tiles = (int)P->rt.size();
       launch_readout_bwd<T>(a, grid_mlp, st);
-      wgrad(buf(L.h[blocks_done]), d, nullptr, 0, buf(L.dr), false, d, d, R.l.w1, acc);
-      bias(buf(L.dr), R.l.b1, -1, 0, 0, acc);
+      wgrad(buf(L.h[blocks_done]), d, nullptr, 0, buf(L.dr), false, d, d, R.l.w1, R.l.b1, -1, 0, acc);
     }
     if (dhest) {
       // ReadoutChEst on the same state: its 2B outputs in groups of 8 columns, adding to dh
@@ -1775,8 +1779,7 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
         c.part = chest_part(g) + (int64_t)ro_done * grid_mlp * 1032;
         launch_readout_bwd<T>(c, grid_mlp, st);
       }
-      wgrad(buf(L.h[blocks_done]), d, nullptr, 0, buf(L.dr), false, d, d, m->ro_ch.w1, acc);
-      bias(buf(L.dr), m->ro_ch.b1, -1, 0, 0, acc);
+      wgrad(buf(L.h[blocks_done]), d, nullptr, 0, buf(L.dr), false, d, d, m->ro_ch.w1, m->ro_ch.b1, -1, 0, acc);
     }
     ++ro_done;
   };
@@ -1790,8 +1793,7 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
     T *h_in = buf(L.h[i]);
     T *a_i = buf(L.a[i]);
     // conv_b: h_{i+1} = h_i + conv_b(a_i)
-    wgrad(a_i, d, nullptr, 0, dh, true, d, d, B.b.w);
-    bias(dh, B.b.b, -1, 0, 0);
+    wgrad(a_i, d, nullptr, 0, dh, true, d, d, B.b.w, B.b.b);
     const int gl = dgrad(dh, bp + B.bg_b, EPI_LN_BWD, NRX_K_CONV_B, dz, a_i, buf(L.z[i]), (const float *)(ws + L.stats[i]),
                          w + B.g);
     launch_ln_reduce(lpart, gl, B.g, B.beta, dw, st);
@@ -1799,8 +1801,7 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
     if (B.mp_round >= 0) {
       const int r = B.mp_round;
       T *agg = buf(L.agg[r]);
-      wgrad(h_in, d, agg, d, dz, true, 2 * d, B.a.cin_total, B.a.w);
-      bias(dz, B.a.b, B.a.w, B.a.cin_total, 2 * d);
+      wgrad(h_in, d, agg, d, dz, true, 2 * d, B.a.cin_total, B.a.w, B.a.b, B.a.w, 2 * d);
       dgrad(dz, bp + B.bg_a_h, EPI_RESID, NRX_K_CONV_A_MP, dh, dh, nullptr, nullptr, nullptr);
       dgrad(dz, bp + B.bg_a_agg, EPI_STORE, NRX_K_CONV_A_MP, buf(L.dagg), nullptr, nullptr, nullptr, nullptr);
       MpBwdArgs<T> ma{};
@@ -1815,13 +1816,10 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
       ma.tiles = D.mt;
       ma.n_tiles = (int)P->mt.size();
       launch_mp_bwd<T>(ma, grid_mlp, st);
-      wgrad(buf(L.m1[r]), d, nullptr, 0, buf(L.dmsg), false, d, d, m->mp[r].w2);
-      bias(buf(L.dmsg), m->mp[r].b2, -1, 0, 0);
-      wgrad(h_in, d, nullptr, 0, buf(L.dm1), false, d, d, m->mp[r].w1);
-      bias(buf(L.dm1), m->mp[r].b1, -1, 0, 0);
+      wgrad(buf(L.m1[r]), d, nullptr, 0, buf(L.dmsg), false, d, d, m->mp[r].w2, m->mp[r].b2);
+      wgrad(h_in, d, nullptr, 0, buf(L.dm1), false, d, d, m->mp[r].w1, m->mp[r].b1);
     } else {
-      wgrad(h_in, d, nullptr, 0, dz, true, d, d, B.a.w);
-      bias(dz, B.a.b, -1, 0, 0);
+      wgrad(h_in, d, nullptr, 0, dz, true, d, d, B.a.w, B.a.b);
       dgrad(dz, bp + B.bg_a_h, EPI_RESID, NRX_K_CONV_A, dh, dh, nullptr, nullptr, nullptr);
     }
   }
@@ -1842,13 +1840,11 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
   const int B4 = 4 * m->cfg.n_ant;
   for (auto &ci : m->cins) {
     if (!ci.m) {
-      wgrad(buf(L.X), m->cx, nullptr, 0, dh, true, B4, B4 + 2, ci.c.w);
-      bias(dh, ci.c.b, ci.c.w, B4 + 2, B4);
+      wgrad(buf(L.X), m->cx, nullptr, 0, dh, true, B4, B4 + 2, ci.c.w, ci.c.b, ci.c.w, B4);
     } else if (batch_uses(P, ci.m)) {
       // Var-IO: this modulation's StateInit sees the gradient of its UEs' rows only
       launch_select_rows<T>(dh, D.geo, P->n, P->max_rows, ci.m, dz, st);
-      wgrad(buf(L.X), m->cx, nullptr, 0, dz, true, B4, B4 + 2, ci.c.w);
-      bias(dz, ci.c.b, ci.c.w, B4 + 2, B4);
+      wgrad(buf(L.X), m->cx, nullptr, 0, dz, true, B4, B4 + 2, ci.c.w, ci.c.b, ci.c.w, B4);
     } else {
       HIPCHK(hipMemsetAsync(dw + ci.c.w, 0, (size_t)(ci.c.b + m->cfg.d - ci.c.w) * sizeof(float), st));
     }

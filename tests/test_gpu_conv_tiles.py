@@ -76,3 +76,35 @@ def test_gradient_of_copies(prec):
                 assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), (n, name)
     finally:
         L.nrx_model_destroy(m)
+
+
+@pytest.mark.parametrize("shapes", [[(1, 3), (2, 4)], [(7, 2), (1, 4), (3, 1), (5, 3)], [(1, 1)] * 9])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_gradient_of_a_batch_is_the_sum_over_its_slots(shapes, prec):
+    """Batches of remainders (tiles shorter than a step, partitions without rows, every UE count side by side): no slot's
+    layers see another's, so the gradient of the batch is the sum of the slots' own up to the rounding of fp32 sums over
+    at most a few thousand rows, 1e-5 of the norm as above."""
+    log(f"conv tiles: gradient of a batch {shapes}, precision {prec}")
+    m, w = _model(prec)
+
+    def gradient(batch, y, dl):
+        slots, sz = L.make_slots(batch, 4)
+        ws = torch.empty(L.nrx_workspace_bytes(m, slots, save_acts=True), dtype=torch.uint8, device="cuda")
+        llr = torch.empty(sz["llr"], device="cuda")
+        dw = torch.full_like(w, float("nan"))
+        L.nrx_forward(m, w, slots, y, llr, ws, save_acts=True)
+        L.nrx_backward(m, w, slots, dl, dw, ws)
+        torch.cuda.synchronize()
+        return dw.double().cpu().numpy()
+    try:
+        batch = [dict(n_prb=p, n_ant=4, n_ue=u, bits=[4] * u, slot_number=i) for i, (p, u) in enumerate(shapes)]
+        g = torch.Generator(device="cuda").manual_seed(9)
+        ys = [torch.randn(2 * 12 * p * 14 * 4, generator=g, device="cuda") for p, _ in shapes]
+        ds = [torch.randn(u * 14 * 12 * p * 4, generator=g, device="cuda") for p, u in shapes]
+        got = gradient(batch, torch.cat(ys), torch.cat(ds))
+        ref = sum(gradient([b], y, d) for b, y, d in zip(batch, ys, ds))
+        for name, off, shape in L.weight_layout(m):
+            a, b = (x[off:off + int(np.prod(shape))] for x in (got, ref))
+            assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), name
+    finally:
+        L.nrx_model_destroy(m)
