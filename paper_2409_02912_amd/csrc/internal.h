@@ -225,7 +225,7 @@ struct SimParams {
 };
 void launch_sim(const SimParams &p, const SlotGeo *geo, const int64_t *tap_off, int n_slots, int64_t max_re,
                 int max_ubl, int m_max, const float2 *dmrs, float2 *g_raw, float2 *g_mix, float *fd_n0, float2 *y,
-                float2 *h_true, uint8_t *bits, float *snr_db, float *n0, int64_t max_bits, hipStream_t st);
+                float2 *h_true, uint8_t *bits, float *snr_db, float *n0, hipStream_t st);
 
 // Backward pass.
 template <typename T>

@@ -126,7 +126,7 @@ struct Plan {
   // with a UE of that modulation, which the Var-IO StateInit and readout launches of that modulation walk
   bool mod_lists = false;
   std::vector<Tile> ctm[NRX_N_MODS][N_TILE_SIZES], rtm[NRX_N_MODS];
-  int64_t rows = 0, max_rows = 0, max_re = 0, max_pairs = 0, max_ute = 0, max_bits = 0;
+  int64_t rows = 0, max_rows = 0, max_re = 0, max_pairs = 0, max_ute = 0;
   int64_t dmrs_total = 0, pairs_total = 0, n_data_bits = 0;
   int max_ubl = 0;
   // device table blob
@@ -277,7 +277,6 @@ nrx_status get_plan(const nrx_slot_desc *d, int n, int max_ant, int m_max, int s
     P->max_re = std::max<int64_t>(P->max_re, (int64_t)g.S * 14);
     P->max_pairs = std::max(P->max_pairs, npairs);
     P->max_ute = std::max<int64_t>(P->max_ute, (int64_t)g.U * 14 * g.S);
-    P->max_bits = std::max<int64_t>(P->max_bits, (int64_t)g.U * 12 * g.S);
     P->max_ubl = std::max(P->max_ubl, ubl);
     int nb = 0;
     for (int u = 0; u < g.U; ++u) nb += g.m[u];
@@ -2249,7 +2248,7 @@ extern "C" nrx_status slot_sim(const nrx_sim_config *cfg, uint64_t seed, uint32_
   sp.batch = batch_index;
   launch_sim(sp, D.geo, D.tap_off, P->n, P->max_re, P->max_ubl, m_max, dmrs, (float2 *)(w + L.graw),
              (float2 *)(w + L.gmix), (float *)(w + L.fd), (float2 *)y, (float2 *)h_true, bits, snr_db, n0,
-             P->max_bits, st);
+             st);
   HIPCHK(hipGetLastError());
   return NRX_OK;
 }

@@ -83,3 +83,30 @@ def test_nothing_beside_the_batch_is_written():
     out = llr.cpu().numpy()
     assert np.all(out[:5] == 7.0) and np.all(out[5 + sz["llr"]:] == 7.0)
     assert not np.any(out[5:5 + sz["llr"]] == 7.0)
+
+
+@pytest.mark.parametrize("n_taps", [1, 3, 7, 12, 24, 32])
+def test_slot_sim_edges(n_taps):
+    """Slot generator at the edges of its workgroups (64 subcarriers, antennas in pairs) and for every way the taps are
+    compiled (counts of their own and the general loop): odd and single antennas, one PRB, symbols of one UE to four, with
+    Doppler and antenna correlation, against the oracle.  Bar: 2e-5 norm-wise as for every slot_sim test (fp32 phases of
+    up to 2 pi carry 2^-22 each, sums over at most 32 taps and 16 sinusoids); bits are exact."""
+    shapes = [_shape(1, 1, 1, [2], 0), _shape(6, 3, 4, [8, 2, 6, 4], 13), _shape(11, 16, 2, [4, 8], 4), _shape(5, 2, 3, [2, 2, 6], 8)]
+    log(f"slot_sim edges: {n_taps} taps")
+    cfg = dict(n_taps=n_taps, decay_ns=200.0, doppler=80.0, rho=0.4, snr=(0.0, 20.0))
+    ref = oracle_batch(shapes, sim_cfg_oracle(cfg), 77, 2, 8)
+    descs, sz = L.make_slots(shapes, 8)
+    c = L.sim_config(n_taps=n_taps, tap_decay_ns=200.0, doppler_max_hz=80.0, rho=0.4, snr_db_lo=0.0, snr_db_hi=20.0)
+    y = torch.full((2 * sz["y"],), float("nan"), device="cuda")
+    h = torch.full((2 * sz["h"],), float("nan"), device="cuda")
+    bits = torch.full((sz["bits"],), 9, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(L.slot_sim_workspace_bytes(c, descs), dtype=torch.uint8, device="cuda")
+    L.slot_sim(c, 77, 2, descs, 8, y, ws, h_true=h, bits=bits)
+    torch.cuda.synchronize()
+    yc, off = y.cpu().numpy().view(np.complex64), 0
+    for got, r in zip(split_h(h.cpu().numpy().view(np.complex64), shapes), ref):
+        assert rel_err(got, r["h"]) < 2e-5
+        n = r["y"].size
+        assert rel_err(yc[off:off + n], r["y"].reshape(-1)) < 2e-5
+        off += n
+    assert np.array_equal(bits.cpu().numpy(), np.concatenate([r["bits"].reshape(-1) for r in ref]))
