@@ -78,7 +78,8 @@ __host__ __device__ __forceinline__ int swz(int h) { return (h >> 1) & 3; }
 // Output-channel permutation used by every MFMA GEMM here: n-block nb, column j
 // of the MFMA output holds channel 8*j + nb, so a lane owns 8 consecutive
 // channels of each of its rows.
-__host__ __device__ __forceinline__ int nperm(int nb, int j) { return 8 * j + nb; }
+// (With four blocks, 64 channels: 4 j + nb.)
+__host__ __device__ __forceinline__ int nperm(int nb, int j, int blocks = 8) { return blocks * j + nb; }
 
 // FP8 (OCP E4M3) MFMA, 16x16x128, unit block scales: lane l holds 32 bytes of
 // A row l%16 and of B column l%16 for k-group l/16; A and B use the same
@@ -133,6 +134,12 @@ __device__ __forceinline__ void row_sum16_n(float (&v)[N]) {
   for (int k = 0; k < N; ++k) v[k] = dpp_add<0x140>(v[k]);
 }
 
+// the value of the lane that the DPP control CTRL selects within each row of 16 lanes
+template <int CTRL>
+__device__ __forceinline__ float dpp_get(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
 // 8 consecutive channels <-> 16/32 bytes
 template <typename T> struct pack8;
 template <> struct pack8<bf16_t> {
@@ -163,6 +170,23 @@ template <> struct pack8<float> {
     for (int i = 0; i < 4; ++i) { a.w[i] = __float_as_uint(x[i]); b.w[i] = __float_as_uint(x[4 + i]); }
     st16(p, a);
     st16(p + 4, b);
+  }
+};
+
+// N consecutive channels (8, or 4 of a 64-channel network's) <-> memory
+template <typename T, int N>
+struct packn : pack8<T> {};
+template <>
+struct packn<bf16_t, 4> {
+  __device__ static __forceinline__ void load(const bf16_t *p, float *o) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    o[0] = __uint_as_float(v.x << 16);
+    o[1] = __uint_as_float(v.x & 0xFFFF0000u);
+    o[2] = __uint_as_float(v.y << 16);
+    o[3] = __uint_as_float(v.y & 0xFFFF0000u);
+  }
+  __device__ static __forceinline__ void store(bf16_t *p, const float *x) {
+    *reinterpret_cast<uint2 *>(p) = make_uint2(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]));
   }
 };
 

@@ -122,13 +122,40 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void *base,
                                            __builtin_amdgcn_readfirstlane(nbytes), 0x00020000);
 }
 
+// Row sums of N rows over a lane's channels and the 16 lanes of the row, every lane receiving them: first(k) is the
+// sum over the lane's channels, add(k, x) the same going on from x.  With 8 channels a lane adds its own and the
+// butterfly the lanes.  A 64-channel network's lane holds 4: the odd lane of a pair goes on from the even lane's
+// sum, and the butterfly runs over the pairs, so that the additions, and with them the last bit, are those of
+// the 128-channel kernels on the same network padded with zeros.
+template <int N, int NBK, typename First, typename Add>
+__device__ __forceinline__ void row_sums(float (&v)[N], First first, Add add) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = first(k);
+  if constexpr (NBK == 8) {
+    row_sum16_n<N>(v);
+  } else {
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = add(k, dpp_get<0xA0>(v[k]));   // quad_perm [0,0,2,2]
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = dpp_get<0xF5>(v[k]);           // quad_perm [1,1,3,3]
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = dpp_add<0x4E>(v[k]);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = dpp_add<0x141>(v[k]);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = dpp_add<0x140>(v[k]);
+  }
+}
+
 // Epilogue of one tile: bias (+ PE field) -> store | LayerNorm + ReLU | residual
-// add | LayerNorm backward.  Lane owns channels 8*lr .. +7 of rows 4*lk + i.
-template <typename T, int MB, int EPI, int LB = (MB % 2 == 0 ? 2 : 1)>
+// add | LayerNorm backward.  Lane owns channels NBK*lr .. of rows 4*lk + i (NBK 8; 4 with rows of 64 channels).
+template <typename T, int MB, int EPI, int LB = (MB % 2 == 0 ? 2 : 1), int NBK = 8>
 __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &tl, const SlotGeo &g,
-                                              f32x4_t (&acc)[MB][8], int wave, int lr, int lk, float *lnp) {
+                                              f32x4_t (&acc)[MB][NBK], int wave, int lr, int lk, float *lnp) {
+  static_assert(NBK == 8 || (NBK == 4 && sizeof(T) == 2 && EPI <= EPI_RESID), "epilogue");
+  constexpr int RW = 16 * NBK;     // channels per row
   const int U = g.U, S = g.S, rps = 14 * U;
-  const int ch0 = 8 * lr;          // this lane's 8 consecutive output channels
+  const int ch0 = NBK * lr;        // this lane's consecutive output channels
   if constexpr (EPI == EPI_LN_BWD) {
     // acc = dL/da with a = ReLU(LN(z)); resid holds a, save_z holds z, save_stats (mean, rstd).
     // dz = rstd (dzhat - mean(dzhat) - zhat mean(dzhat zhat)), dzhat = g * dn, dn = da [a > 0]
@@ -168,9 +195,9 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
     return;
   }
   constexpr bool LN = EPI == EPI_LN_RELU || EPI == EPI_LN_RELU_SAVE;
-  float bias[8];
+  float bias[NBK];
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) bias[nb] = a.bias[ch0 + nb];
+  for (int nb = 0; nb < NBK; ++nb) bias[nb] = a.bias[ch0 + nb];
 
   // PE field: its row is fixed by (subcarrier class, symbol), found with float
   // reciprocals (quotients below 2^12 with at least 0.5/rps to the next integer, far
@@ -181,7 +208,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
     constexpr int PB = 1;
 #pragma unroll
     for (int mb0 = 0; mb0 < MB; mb0 += PB) {
-      float pev[PB][4][8];
+      float pev[PB][4][NBK];
 #pragma unroll
       for (int q = 0; q < PB; ++q)
 #pragma unroll
@@ -195,23 +222,25 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
           const int par = (s - (u >> 1)) & 1;
           const int edge = s == 0 ? 1 : (s == S - 1 ? 2 : 0);
           const float4 *pf = reinterpret_cast<const float4 *>(a.pe + ((size_t)((par * 3 + edge) * 14 + t)) * NRX_D + ch0);
-          const float4 x0 = pf[0], x1 = pf[1];
-          pev[q][i][0] = x0.x; pev[q][i][1] = x0.y; pev[q][i][2] = x0.z; pev[q][i][3] = x0.w;
-          pev[q][i][4] = x1.x; pev[q][i][5] = x1.y; pev[q][i][6] = x1.z; pev[q][i][7] = x1.w;
+#pragma unroll
+          for (int w = 0; w < NBK / 4; ++w) {
+            const float4 x = pf[w];
+            pev[q][i][4 * w] = x.x; pev[q][i][4 * w + 1] = x.y; pev[q][i][4 * w + 2] = x.z; pev[q][i][4 * w + 3] = x.w;
+          }
         }
 #pragma unroll
       for (int q = 0; q < PB; ++q)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) acc[mb0 + q][nb][i] += pev[q][i][nb];
+          for (int nb = 0; nb < NBK; ++nb) acc[mb0 + q][nb][i] += pev[q][i][nb];
     }
   }
 
   if constexpr (LN) {
-    float lng[8], lnb[8];
+    float lng[NBK], lnb[NBK];
 #pragma unroll
-    for (int nb = 0; nb < 8; ++nb) { lng[nb] = a.ln_g[ch0 + nb]; lnb[nb] = a.ln_b[ch0 + nb]; }
+    for (int nb = 0; nb < NBK; ++nb) { lng[nb] = a.ln_g[ch0 + nb]; lnb[nb] = a.ln_b[ch0 + nb]; }
     // statistics of LB m-blocks (4 LB rows) together: every butterfly step of the row
     // sums runs over all of them before the next, so the steps do not wait on each other
 #pragma unroll
@@ -220,33 +249,41 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
 #pragma unroll
       for (int q = 0; q < LB; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float sm = 0.f;
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) {
-            acc[mb0 + q][nb][i] += bias[nb];
-            sm += acc[mb0 + q][nb][i];
-          }
-          mean[4 * q + i] = sm;
-        }
-      row_sum16_n<LB * 4>(mean);
+          for (int nb = 0; nb < NBK; ++nb) acc[mb0 + q][nb][i] += bias[nb];
+      auto x = [&](int k, int nb) { return acc[mb0 + k / 4][nb][k % 4]; };
+      auto sum = [&](int k, float s) {
+#pragma unroll
+        for (int nb = 0; nb < NBK; ++nb) s += x(k, nb);
+        return s;
+      };
+      row_sums<LB * 4, NBK>(mean, [&](int k) { return sum(k, 0.f); }, sum);
 #pragma unroll
       for (int k = 0; k < LB * 4; ++k) mean[k] *= a.ln_inv;
       // channels at or beyond the state depth carry exact zeros (zero weights and bias):
-      // each adds mean^2 to the sum of squared deviations, removed in one step
+      // each adds mean^2 to the sum of squared deviations, removed in one step.  (The fused products are spelled
+      // out: the last bit of the statistics decides roundings to 16 bits further on.)
+      auto dev = [&](int k, int nb) { return x(k, nb) - mean[k]; };
+      auto squares = [&](int k, float s, int from) {
 #pragma unroll
-      for (int q = 0; q < LB; ++q)
+        for (int nb = from; nb < NBK; ++nb) s = fmaf(dev(k, nb), dev(k, nb), s);
+        return s;
+      };
+      row_sums<LB * 4, NBK>(
+          rstd, [&](int k) { return squares(k, fmaf(dev(k, 0), dev(k, 0), dev(k, 1) * dev(k, 1)), 2); },
+          [&](int k, float s) { return squares(k, s, 0); });
+      if constexpr (NBK == 4) {
+        // (channels 64 .. 127 of the padded network, which are not here, would have added theirs: eight groups of
+        // eight, all alike)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float sq = 0.f;
+        for (int k = 0; k < LB * 4; ++k) {
+          float z = fmaf(mean[k], mean[k], mean[k] * mean[k]);
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) {
-            const float dv = acc[mb0 + q][nb][i] - mean[4 * q + i];
-            sq += dv * dv;
-          }
-          rstd[4 * q + i] = sq;
+          for (int c = 2; c < 8; ++c) z = fmaf(mean[k], mean[k], z);
+          rstd[k] += 8.f * z;
         }
-      row_sum16_n<LB * 4>(rstd);
+      }
 #pragma unroll
       for (int k = 0; k < LB * 4; ++k) {
         const float var = fmaxf(rstd[k] - a.ln_pad * mean[k] * mean[k], 0.f) * a.ln_inv;
@@ -260,9 +297,9 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
             const int r = wave * 16 * MB + (mb0 + q) * 16 + 4 * lk + i;
             if (r < tl.nrows) {
               const int64_t grow = g.row_base + tl.row0 + r;
-              float z[8];
+              float z[NBK];
 #pragma unroll
-              for (int nb = 0; nb < 8; ++nb) z[nb] = acc[mb0 + q][nb][i];
+              for (int nb = 0; nb < NBK; ++nb) z[nb] = acc[mb0 + q][nb][i];
               pack8<T>::store(a.save_z + grow * NRX_D + ch0, z);
               if (lr == 0) { a.save_stats[2 * grow] = mean[4 * q + i]; a.save_stats[2 * grow + 1] = rstd[4 * q + i]; }
             }
@@ -273,7 +310,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) {
+          for (int nb = 0; nb < NBK; ++nb) {
             const float n = (acc[mb0 + q][nb][i] - mean[4 * q + i]) * (rstd[4 * q + i] * lng[nb]) + lnb[nb];
             acc[mb0 + q][nb][i] = n > 0.f ? n : 0.f;
           }
@@ -291,7 +328,8 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
   // residual rows of the lane (EPI_RESID), requested RB m-blocks at a time before any of
   // them is used; rows past the tile read row 0 and are not stored
   constexpr int RB = MB % 2 == 0 ? 2 : 1;
-  v16 rraw[EPI == EPI_RESID ? RB : 1][4];
+  float rres[EPI == EPI_RESID && NBK == 4 ? RB : 1][4][4];
+  v16 rraw[EPI == EPI_RESID && NBK == 8 ? RB : 1][4];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     if constexpr (EPI == EPI_RESID && sizeof(T) == 2) {
@@ -302,7 +340,8 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
           for (int i = 0; i < 4; ++i) {
             const int r = wave * 16 * MB + (mb + q) * 16 + 4 * lk + i;
             const int64_t grow = g.row_base + tl.row0 + (r < tl.nrows ? r : 0);
-            rraw[q][i] = ld16(a.resid + grow * NRX_D + ch0);
+            if constexpr (NBK == 8) rraw[q][i] = ld16(a.resid + grow * RW + ch0);
+            else packn<T, NBK>::load(a.resid + grow * RW + ch0, rres[q][i]);
           }
       }
       // keeps the scheduler from hoisting the next batch above this m-block's stores
@@ -314,11 +353,14 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
       const int r = wave * 16 * MB + mb * 16 + 4 * lk + i;
       const bool valid = r < tl.nrows;
       const int64_t grow = g.row_base + tl.row0 + (valid ? r : 0);
-      float v[8];
+      float v[NBK];
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) v[nb] = LN ? acc[mb][nb][i] : acc[mb][nb][i] + bias[nb];
+      for (int nb = 0; nb < NBK; ++nb) v[nb] = LN ? acc[mb][nb][i] : acc[mb][nb][i] + bias[nb];
       if constexpr (EPI == EPI_RESID) {
-        if constexpr (sizeof(T) == 2) {
+        if constexpr (NBK == 4) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] += rres[mb % RB][i][k];
+        } else if constexpr (sizeof(T) == 2) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             v[2 * k] += __uint_as_float(rraw[mb % RB][i].w[k] << 16);
@@ -328,7 +370,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
           float rsd[8];
           pack8<T>::load(a.resid + grow * NRX_D + ch0, rsd);
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) v[nb] += rsd[nb];
+          for (int nb = 0; nb < NBK; ++nb) v[nb] += rsd[nb];
         }
       }
       bool keep = valid;
@@ -339,11 +381,12 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs<T> &a, const Tile &
         }
       }
       if (keep) {
-        if (a.out) pack8<T>::store(a.out + grow * NRX_D + ch0, v);
-        if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * NRX_D + ch0) = fp8x8(v, a.out8_inv);
+        if (a.out) packn<T, NBK>::store(a.out + grow * RW + ch0, v);
+        if constexpr (NBK == 8)
+          if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * NRX_D + ch0) = fp8x8(v, a.out8_inv);
         if (a.amax) {
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) vmax = fmaxf(vmax, fabsf(v[nb]));
+          for (int nb = 0; nb < NBK; ++nb) vmax = fmaxf(vmax, fabsf(v[nb]));
         }
       }
     }

@@ -272,10 +272,12 @@ __device__ __forceinline__ void conv_ring_body(const ConvArgs<T> &a, const Src &
 // workgroup, 34 -> 31 us, and 17 us in 128-row tiles.  The results are the ring's bit for bit: the products are
 // accumulated in the same order whatever the tile.
 constexpr int TAP_SLOTS = 7;
-constexpr int TAP_BYTES = 8 * 16 * ROWB;   // one tap of a 64-byte K chunk: 128 output channels
 
-template <int MB, int NW>
+// NBK: 16-channel blocks of the output, 8, or 4 for networks of up to 64 channels (rows of 64 channels, half the
+// K chunks and half the products per chunk of the same network padded to 128)
+template <int MB, int NW, int NBK = 8>
 struct PipeShape {
+  static constexpr int TAP_BYTES = NBK * 16 * ROWB;   // one tap of a 64-byte K chunk
   static constexpr int TILE = 16 * MB * NW;
   static constexpr int APW = (halo_rows_max(TILE) / 16 + NW - 1) / NW;   // halo copies per wave
   static constexpr int AROWS = APW * NW * 16;
@@ -284,13 +286,12 @@ struct PipeShape {
   static constexpr int LDS_BYTES = 2 * ABYTES + TAP_SLOTS * TAP_BYTES;
 };
 
-template <typename T, int EPI, int MB, int NW, typename Src>
+template <typename T, int EPI, int MB, int NW, int NBK = 8, typename Src>
 __device__ __forceinline__ void conv_pipe_body(const ConvArgs<T> &a, const Src &src, lds_u8 *lds, float *lnp) {
-  using Sh = PipeShape<MB, NW>;
-  constexpr int APW = Sh::APW, ZROW = Sh::ZROW;
+  using Sh = PipeShape<MB, NW, NBK>;
+  constexpr int APW = Sh::APW, ZROW = Sh::ZROW, TAP_BYTES = Sh::TAP_BYTES;
   constexpr int KC = 64 / (int)sizeof(T);
-  constexpr int BPT = 8 / NW;                      // weight copies per wave and tap
-  static_assert(8 % NW == 0 && APW < 16, "shape");
+  static_assert(APW < 16, "vmcnt immediate below");
   constexpr int WAIT_KEEP_A = (0xF << 8) | (7 << 4) | APW;
   auto lds_a = [&](int b) { return lds + b * Sh::ABYTES; };
   lds_u8 *lds_b = lds + 2 * Sh::ABYTES;
@@ -309,8 +310,9 @@ __device__ __forceinline__ void conv_pipe_body(const ConvArgs<T> &a, const Src &
   const uint32_t wlane = (uint32_t)((lane >> 2) * ROWB + (((lane & 3) ^ swz(lane >> 2)) << 4));
   auto stage_tap = [&](int tap, int slot) {
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) {
+    for (int j = 0; j < (NBK + NW - 1) / NW; ++j) {
       const int ins = wave + NW * j;
+      if (ins >= NBK) break;   // (with NBK < NW the last waves copy none)
       dma16(wrs, lds_addr(lds_b + slot * TAP_BYTES + ins * 1024), wlane + (uint32_t)(tap * TAP_BYTES + ins * 1024));
     }
   };
@@ -371,11 +373,11 @@ __device__ __forceinline__ void conv_pipe_body(const ConvArgs<T> &a, const Src &
       tt[mb] = r < tl.nrows ? (R - s * q.rps) / q.U : -1;
       hc[mb] = R - q.rel0;
     }
-    f32x4_t acc[MB][8];
+    f32x4_t acc[MB][NBK];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < NBK; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // activation fragments of the tap (di, dj) from halo buffer la
     auto load_a = [&](const lds_u8 *la, int di, int dj, v16 *af) {
@@ -413,21 +415,21 @@ __device__ __forceinline__ void conv_pipe_body(const ConvArgs<T> &a, const Src &
 #pragma unroll
       for (int j = 0; j < 4; ++j) lbs[j] = lds_b + slot_after(rd, j) * TAP_BYTES + blane;
 #pragma unroll
-      for (int i = 0; i < 24; ++i) {
-        const int nb = i & 7, tg = i / 8;
+      for (int i = 0; i < 3 * NBK; ++i) {
+        const int nb = i % NBK, tg = i / NBK;
         // the wave priority falls through the group: of the two waves of a SIMD the one behind is issued first
         if (i == 0) __builtin_amdgcn_s_setprio(3);
-        else if (i == 6) __builtin_amdgcn_s_setprio(2);
-        else if (i == 12) __builtin_amdgcn_s_setprio(1);
-        else if (i == 18) __builtin_amdgcn_s_setprio(0);
-        const v16 b2 = ld16(lbs[(i + 2) / 8] + ((i + 2) & 7) * 1024);
-        if (nb == 4) {
+        else if (i == 3 * NBK / 4) __builtin_amdgcn_s_setprio(2);
+        else if (i == 3 * NBK / 2) __builtin_amdgcn_s_setprio(1);
+        else if (i == 9 * NBK / 4) __builtin_amdgcn_s_setprio(0);
+        const v16 b2 = ld16(lbs[(i + 2) / NBK] + ((i + 2) % NBK) * 1024);
+        if (nb == NBK / 2) {
           if (tg < 2) load_a(la, grp - 1, tg, afn);
           else load_a(la_next, grp == 2 ? -1 : grp, -1, afn);
         }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = mma<T>::run(afc[mb], b0, acc[mb][nb]);
-        if (nb == 7) {
+        if (nb == NBK - 1) {
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb) afc[mb] = afn[mb];
         }
@@ -441,7 +443,7 @@ __device__ __forceinline__ void conv_pipe_body(const ConvArgs<T> &a, const Src &
       rd = slot_after(rd, 3);
       if (grp == 2) ka += 1;
     }
-    conv_epilogue<T, MB, EPI>(a, tl, ldc_geo(a.geo + tl.slot), acc, wave, lr, lk, lnp);
+    conv_epilogue<T, MB, EPI, (MB % 2 == 0 ? 2 : 1), NBK>(a, tl, ldc_geo(a.geo + tl.slot), acc, wave, lr, lk, lnp);
   }
   __builtin_amdgcn_s_waitcnt(0);   // no copy into LDS outlives the call
 }

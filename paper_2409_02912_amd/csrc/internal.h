@@ -73,6 +73,9 @@ void launch_prep_fp8(const float *w, const Fp8Job *jobs, int n_jobs, uint8_t *w8
 template <typename T>
 void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, hipStream_t st);
 
+// BF16 inference of networks with d <= 64: rows of 64 channels, tiles of 128 mb rows.
+void launch_conv_narrow(const ConvArgs<bf16_t> &a, int epi, int mb, int grid, hipStream_t st);
+
 // Weight preparation: fp32 master -> MFMA operand layouts and PE fields.
 struct PrepJob {
   int32_t kind;        // 0 conv, 1 dense, 2 PE field, 3 conv transposed+flipped (dgrad), 4 narrow dense,
@@ -86,7 +89,9 @@ struct PrepJob {
   int64_t dst;         // element offset into the prepped (T) or field (fp32) buffer
   int64_t count;       // prepped elements of this job
   int32_t d_out;       // output columns of the master conv/dense tensor (the state depth d <= 128)
-  int32_t seg;         // master input channels per 128-wide activation segment (0: identity map)
+  int32_t seg;         // master input channels per activation segment of width channels (0: identity map)
+  int32_t width;       // output columns of the prepped operand (and channels per activation segment): 128 or 64
+  int32_t pad;
 };
 
 template <typename T>
@@ -130,6 +135,7 @@ struct MlpArgs {
                                   // ([s][t][u][b] complex at geo.h_off), outputs j < 2B of the slot
   int n_out;                      // readout: columns of w2 / b2 (0: m_max)
   int only_m;                     // readout (Var-IO): write only the rows of UEs with this many bits (0: all)
+  int width;                      // channels per row: 128, or 64 (BF16 inference of networks with d <= 64)
 };
 template <typename T>
 void launch_mp(const MlpArgs<T> &a, int grid, hipStream_t st);

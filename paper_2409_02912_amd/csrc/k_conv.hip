@@ -390,6 +390,16 @@ __global__ __launch_bounds__(64 * NW, OCC) void conv3x3_ring_kernel(ConvArgs<T> 
                           lane >> 4);
 }
 
+// The default kernel on rows of 64 channels (networks of state depth d <= 64, BF16 inference): a quarter of the
+// products of the same network padded to 128.  44,352 rows, us: conv 23 -> 14, conv after message passing 37 -> 20
+// (event times, about 5 us of them the launch's), a slot of 132 PRB through 8 iterations 627 -> 342.
+template <int EPI, int MB>
+__global__ __launch_bounds__(512, 1) void conv3x3_narrow_kernel(ConvArgs<bf16_t> a) {
+  __shared__ __align__(16) unsigned char lds[PipeShape<MB, 8, 4>::LDS_BYTES];
+  float lnp[1];
+  conv_pipe_body<bf16_t, EPI, MB, 8, 4>(a, GridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds, lnp);
+}
+
 }  // namespace
 
 // Compiled shapes: rows per wave (16*MB), waves per SIMD, B-operand prefetch.
@@ -480,6 +490,20 @@ void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, h
   if (mb == 2) NRX_RING_CASE(14, 2, 8, 3, 1, 7, 4, 0, 0)
   NRX_RING_CASE(14, 1, 8, 3, 1, 7, 4, 0, 0)
 #undef NRX_RING_CASE
+}
+
+void launch_conv_narrow(const ConvArgs<bf16_t> &a, int epi, int mb, int grid, hipStream_t st) {
+  auto run = [&](auto store, auto ln, auto resid) {
+    auto k = epi == EPI_STORE ? store : (epi == EPI_LN_RELU ? ln : resid);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, a);
+  };
+#define NRX_NARROW(M) \
+  run(conv3x3_narrow_kernel<EPI_STORE, M>, conv3x3_narrow_kernel<EPI_LN_RELU, M>, conv3x3_narrow_kernel<EPI_RESID, M>)
+  if (mb == 4) NRX_NARROW(4);
+  else if (mb == 3) NRX_NARROW(3);
+  else if (mb == 2) NRX_NARROW(2);
+  else NRX_NARROW(1);
+#undef NRX_NARROW
 }
 
 template void launch_conv<float>(const ConvArgs<float> &, int, int, int, int, hipStream_t);

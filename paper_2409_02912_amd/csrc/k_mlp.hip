@@ -146,16 +146,16 @@ __global__ __launch_bounds__(256) void mp_kernel(MlpArgs<T> a) {
   if (a.amax) atomicMax(a.amax, __float_as_uint(vmax));
 }
 
-template <int NW>
+template <int NW, int W>
 __global__ __launch_bounds__(64 * NW, 1) void mp_lds_kernel(MlpArgs<bf16_t> a) {
-  __shared__ __align__(16) unsigned char lds[MP_LDS_BYTES];
-  mp_lds_body<NW>(a, MlpGridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds);
+  __shared__ __align__(16) unsigned char lds[MlpShape<W>::MP_LDS];
+  mp_lds_body<NW, W>(a, MlpGridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds);
 }
 
-template <int NW>
+template <int NW, int W>
 __global__ __launch_bounds__(64 * NW, 1) void readout_lds_kernel(MlpArgs<bf16_t> a) {
-  __shared__ __align__(16) unsigned char lds[RO_LDS_BYTES];
-  readout_lds_body<NW>(a, MlpGridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds);
+  __shared__ __align__(16) unsigned char lds[MlpShape<W>::RO_LDS];
+  readout_lds_body<NW, W>(a, MlpGridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds);
 }
 
 template <typename T>
@@ -297,7 +297,8 @@ void launch_mp(const MlpArgs<T> &a, int grid, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
     // inference: LDS-staged kernel (the training forward keeps the hidden activations: generic kernel)
     if (!a.save_m1) {
-      hipLaunchKernelGGL(mp_lds_kernel<8>, dim3(grid), dim3(512), 0, st, a);
+      if (a.width == 64) hipLaunchKernelGGL((mp_lds_kernel<8, 64>), dim3(grid), dim3(512), 0, st, a);
+      else hipLaunchKernelGGL((mp_lds_kernel<8, NRX_D>), dim3(grid), dim3(512), 0, st, a);
       return;
     }
   }
@@ -307,7 +308,8 @@ template <typename T>
 void launch_readout(const MlpArgs<T> &a, int grid, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
     if (!a.save_m1) {
-      hipLaunchKernelGGL(readout_lds_kernel<8>, dim3(grid), dim3(512), 0, st, a);
+      if (a.width == 64) hipLaunchKernelGGL((readout_lds_kernel<8, 64>), dim3(grid), dim3(512), 0, st, a);
+      else hipLaunchKernelGGL((readout_lds_kernel<8, NRX_D>), dim3(grid), dim3(512), 0, st, a);
       return;
     }
   }

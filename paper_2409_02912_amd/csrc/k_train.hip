@@ -77,11 +77,12 @@ __global__ void prep_kernel(const float *w, const PrepJob *jobs, int n_jobs, int
     wprep[J.dst + k] = elem<T>::from_f(j < J.n_out && c < J.cin_real ? w[J.src + (int64_t)c * J.n_out + j] : 0.f);
     return;
   }
-  const int j = (k / KC) % 16, nb = (k / (16 * KC)) % 8;
-  const int n = nperm(nb, j);
+  const int nblk = J.width / 16;
+  const int j = (k / KC) % 16, nb = (k / (16 * KC)) % nblk;
+  const int n = nperm(nb, j, nblk);
   float v = 0.f;
   if (J.kind == 1) {
-    const int chunk = k / (128 * KC);
+    const int chunk = k / (J.width * KC);
     const int c = chunk * KC + kl;
     if (c < J.cin_real && n < J.d_out) v = w[J.src + (int64_t)c * J.d_out + n];
   } else if (J.kind == 5) {
@@ -90,12 +91,12 @@ __global__ void prep_kernel(const float *w, const PrepJob *jobs, int n_jobs, int
     const int c = chunk * KC + kl;
     v = w[J.src + (int64_t)n * NRX_D + c];
   } else {
-    const int tap = (k / (128 * KC)) % 9, chunk = k / (1152 * KC);
+    const int tap = (k / (J.width * KC)) % 9, chunk = k / (9 * J.width * KC);
     const int c = chunk * KC + kl;
     if (J.kind == 0) {
-      // activation channel c -> master input channel (block convs: 128-wide segments of d channels)
-      const int cm = J.seg ? (c / NRX_D) * J.seg + (c % NRX_D) : c;
-      const bool in = J.seg ? (c % NRX_D) < J.seg : true;
+      // activation channel c -> master input channel (block convs: segments of d of width channels)
+      const int cm = J.seg ? (c / J.width) * J.seg + (c % J.width) : c;
+      const bool in = J.seg ? (c % J.width) < J.seg : true;
       if (in && cm < J.cin_real && n < J.d_out) v = w[J.src + ((int64_t)tap * J.cin_total + cm) * J.d_out + n];
     } else {
       // transposed, flipped: K = original output channel c, N = original input channel cin_first + n

@@ -76,6 +76,7 @@ int conv_mb(const std::vector<Tile> *ct, double over, int max_mb) {
   }
   return best;
 }
+constexpr double CONV_OVER_NARROW = 5.0;   // 64-channel rows: a tap's weights, not its products, are most of a round
 template <typename T>
 constexpr double conv_over = sizeof(T) == 2 ? 0.8 : 0.17;
 inline int variant_tiles(const ConvVariant &v) { return v.aligned ? ALIGNED_TILES : tile_size_index(v.mb); }
@@ -476,6 +477,9 @@ struct nrx_model {
   int64_t bprep_elems = 0;
   void *pinned_bjobs = nullptr;
   size_t tsize = 4;                     // bytes per activation / operand element
+  // channels per activation row: 128, or 64 for BF16 inference of networks with d <= 64 (which do not train; the
+  // persistent kernel has the 128-channel bodies only)
+  int width = NRX_D;
   Graphs *graphs = nullptr;        // captured forward graphs (flags bit 0)
   // FP8 models: E4M3 conv operands with per-layer activation scales
   //   act_scale[i] (i < C): input h_i of block i; [C + i]: conv_a output of block i;
@@ -553,6 +557,7 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
   auto m = std::make_unique<nrx_model>();
   m->chest = (c.flags & 2) != 0;
   m->cfg = c;
+  if (c.precision == NRX_BF16 && c.d <= 64 && !(c.flags & 8)) m->width = 64;
   m->tsize = c.precision == NRX_FP32 ? 4 : 2;   // FP8 models keep BF16 for everything but the block convs
   m->fp8 = c.precision == NRX_FP8;
   // convolution variants until nrx_conv_variant / nrx_autotune choose others: the fastest at the headline
@@ -614,19 +619,19 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
   auto conv_job = [&](ConvLayer &L, int64_t w, int64_t b, int cin_real, int cin_total, int cin_pad, bool pe, int seg) {
     L.w = w; L.b = b; L.cin_real = cin_real; L.cin_total = cin_total; L.n_chunks = cin_pad / KC;
     L.prep = m->prep_elems;
-    PrepJob j{0, cin_real, cin_total, L.n_chunks, 0, 0, w, L.prep, (int64_t)cin_pad * 9 * 128, d, seg};
+    PrepJob j{0, cin_real, cin_total, L.n_chunks, 0, 0, w, L.prep, (int64_t)cin_pad * 9 * m->width, d, seg, m->width, 0};
     m->jobs.push_back(j);
     m->prep_elems += j.count;
     if (pe) {
       L.field = m->field_elems;
-      PrepJob f{2, cin_real, cin_total, 0, 0, 0, w, L.field, 2 * 3 * 14 * 128, d, 0};
+      PrepJob f{2, cin_real, cin_total, 0, 0, 0, w, L.field, 2 * 3 * 14 * 128, d, 0, NRX_D, 0};
       m->jobs.push_back(f);
       m->field_elems += f.count;
     }
   };
   auto dense_job = [&](int64_t w, int64_t &p) {
     p = m->prep_elems;
-    PrepJob j{1, d, d, NRX_D / KC, 0, 0, w, p, (int64_t)NRX_D * 128, d, 0};
+    PrepJob j{1, d, d, m->width / KC, 0, 0, w, p, (int64_t)m->width * m->width, d, 0, m->width, 0};
     m->jobs.push_back(j);
     m->prep_elems += j.count;
   };
@@ -647,10 +652,10 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
       if (mpb[r] == i) L.mp_round = r;
     const bool isb = L.mp_round >= 0;
     conv_job(L.a, toff(m.get(), p + ".conv_a.w"), toff(m.get(), p + ".conv_a.b"), isb ? 2 * d : d,
-             isb ? 2 * d + 2 : d, isb ? 2 * NRX_D : NRX_D, isb, d);
+             isb ? 2 * d + 2 : d, isb ? 2 * m->width : m->width, isb, d);
     L.g = toff(m.get(), p + ".ln.g");
     L.beta = toff(m.get(), p + ".ln.b");
-    conv_job(L.b, toff(m.get(), p + ".conv_b.w"), toff(m.get(), p + ".conv_b.b"), d, d, NRX_D, false, d);
+    conv_job(L.b, toff(m.get(), p + ".conv_b.w"), toff(m.get(), p + ".conv_b.b"), d, d, m->width, false, d);
     if (m->fp8) {
       for (ConvLayer *cl : {&L.a, &L.b}) {
         cl->w8 = m->w8_bytes;
@@ -678,7 +683,7 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
     R.l.w2 = toff(m.get(), p + "w2"); R.l.b2 = toff(m.get(), p + "b2");
     dense_job(R.l.w1, R.l.p1);
     R.l.p2 = m->prep_elems;
-    PrepJob j{4, d, d, NRX_D / KC, 0, mm ? mm : c.m_max, R.l.w2, R.l.p2, (int64_t)NRX_D * 16, d, 0};
+    PrepJob j{4, d, d, m->width / KC, 0, mm ? mm : c.m_max, R.l.w2, R.l.p2, (int64_t)m->width * 16, d, 0, 16, 0};
     m->jobs.push_back(j);
     m->prep_elems += j.count;
     m->ros.push_back(R);
@@ -689,14 +694,14 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
     L.w2 = toff(m.get(), "readout_ch.w2"); L.b2 = toff(m.get(), "readout_ch.b2");
     dense_job(L.w1, L.p1);
     L.p2 = m->prep_elems;
-    PrepJob j{4, d, d, NRX_D / KC, 0, 2 * B, L.w2, L.p2, (int64_t)NRX_D * 16, d, 0};
+    PrepJob j{4, d, d, m->width / KC, 0, 2 * B, L.w2, L.p2, (int64_t)m->width * 16, d, 0, 16, 0};
     m->jobs.push_back(j);
     m->prep_elems += j.count;
   }
   // backward jobs: flipped/transposed conv weights and transposed dense weights
   auto bjob = [&](int kind, int64_t src, int cin_total, int cin_first, int64_t count) {
     const int64_t off = m->bprep_elems;
-    m->bjobs.push_back(PrepJob{kind, d, cin_total, d / KC, cin_first, 0, src, off, count, d, 0});
+    m->bjobs.push_back(PrepJob{kind, d, cin_total, d / KC, cin_first, 0, src, off, count, d, 0, NRX_D, 0});
     m->bprep_elems += count;
     return off;
   };
@@ -725,7 +730,7 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
     if (m->chest) pad_vec(m->ro_ch.b1, &m->ro_ch.b1pad);
     for (auto &pv : pads) {
       *pv.second = m->field_elems;
-      m->jobs.push_back(PrepJob{6, d, d, 0, 0, 0, pv.first, m->field_elems, NRX_D, d, 0});
+      m->jobs.push_back(PrepJob{6, d, d, 0, 0, 0, pv.first, m->field_elems, NRX_D, d, 0, NRX_D, 0});
       m->field_elems += NRX_D;
     }
   }
@@ -1024,6 +1029,17 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       add_stage(epi == EPI_STORE ? PK_CONV_STORE : (epi == EPI_LN_RELU ? PK_CONV_LN : PK_CONV_RESID), &ca);
       return;
     }
+    if constexpr (std::is_same<T, bf16_t>::value) {
+      if (m->width == 64) {
+        const std::vector<Tile> *ct = ca.only_m && P->mod_lists ? P->ctm[ca.only_m / 2 - 1] : P->ct;
+        const int mb = conv_mb(ct, CONV_OVER_NARROW, 4);
+        ca.tiles = ca.only_m && P->mod_lists ? D.ctm[ca.only_m / 2 - 1][mb - 1] : D.ct[mb - 1];
+        ca.n_tiles = (int)ct[mb - 1].size();
+        ProfMark pm(m, cls, st);
+        launch_conv_narrow(ca, epi, mb, (std::min(ca.n_tiles, num_cu()) + 7) / 8 * 8, st);
+        return;
+      }
+    }
     int v = m->conv_variant[cls];
     if (fp8op) v = std::min(v, NRX_CONV8_VARIANTS - 1);
     else if (m->fp8 && cls != NRX_K_CONV_IN) v = CONV_DEFAULT_VARIANT;   // a block conv kept in BF16
@@ -1098,6 +1114,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       ra.geo = D.geo;
       ra.tiles = D.rt;
       ra.n_tiles = (int)P->rt.size();
+      ra.width = m->width;
       // the pass completes at the last launch of the last readout
       const bool fin = last && i + 1 == ros_run.size();
       if (R.m && P->mod_lists && !fin && !persist) {   // Var-IO: only the slots with a UE of this modulation
@@ -1158,6 +1175,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       ma.geo = D.geo;
       ma.tiles = D.mt;
       ma.n_tiles = (int)P->mt.size();
+      ma.width = m->width;
       if (persist) {
         add_stage(PK_MP, &ma);
       } else {
@@ -1166,8 +1184,8 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       }
     }
     ConvArgs<T> ca = a;
-    ca.src0 = h_in; ca.c0 = NRX_D;
-    ca.src1 = agg; ca.c1 = agg ? NRX_D : 0;
+    ca.src0 = h_in; ca.c0 = m->width;
+    ca.src1 = agg; ca.c1 = agg ? m->width : 0;
     ca.w = wprep + B.a.prep;
     ca.bias = vec(B.a.b, B.a.bpad);
     ca.pe = B.a.field >= 0 ? fields + B.a.field : nullptr;
@@ -1190,7 +1208,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     if (amax) ca.amax = amax + C + i;
     conv(ca, save ? EPI_LN_RELU_SAVE : EPI_LN_RELU, agg ? NRX_K_CONV_A_MP : NRX_K_CONV_A, f8a);
     ConvArgs<T> cb = a;
-    cb.src0 = abuf; cb.c0 = NRX_D; cb.src1 = nullptr; cb.c1 = 0;
+    cb.src0 = abuf; cb.c0 = m->width; cb.src1 = nullptr; cb.c1 = 0;
     cb.w = wprep + B.b.prep;
     cb.bias = vec(B.b.b, B.b.bpad);
     cb.pe = nullptr;

@@ -19,19 +19,41 @@ constexpr int MLP_MB = 2;
 // column, which for U = 1, 2, 4 are whole REs (tiles start on RE boundaries);
 // U = 3 goes through LDS.  NW waves share a 128-row tile (8 waves: 16 rows each,
 // two waves per SIMD to cover LDS latency).
-namespace mp2 {
-constexpr int AROWB = NRX_D * 2;         // bytes per activation row (bf16)
-constexpr int TILEB = MLP_ROWS * AROWB;  // 32 KB
-constexpr int WB = NRX_D * NRX_D * 2;    // 32 KB per weight matrix
-constexpr int W2B = 4 * 16 * 64;         // readout second layer, prepped [chunk][16][32] bf16
-__device__ __forceinline__ int apos(int row, int piece) { return row * AROWB + ((piece ^ (row & 15)) << 4); }
-__device__ __forceinline__ int wpos(int c, int nb, int j, int lk) {
-  const int row = (c * 8 + nb) * 16 + j;   // 64-byte rows of the prepped [chunk][nb][16][32] operand
-  return row * 64 + ((lk ^ swz(row)) << 4);
-}
-}  // namespace mp2
-constexpr int MP_LDS_BYTES = 2 * mp2::WB + 2 * mp2::TILEB;
-constexpr int RO_LDS_BYTES = mp2::WB + mp2::W2B + 2 * mp2::TILEB;
+// W: channels per row, 128, or 64 for networks of up to 64 channels; a lane owns W / 16 consecutive channels.
+template <int W>
+struct MlpShape {
+  static constexpr int NB = W / 16;              // 16-column blocks
+  static constexpr int CH = W / 32;              // K chunks
+  static constexpr int PIECES = W / 8;           // 16-byte pieces of a row
+  static constexpr int AROWB = W * 2;            // bytes per activation row (bf16)
+  static constexpr int TILEB = MLP_ROWS * AROWB;
+  static constexpr int WB = W * W * 2;           // bytes per weight matrix
+  static constexpr int W2B = CH * 16 * 64;       // readout second layer, prepped [chunk][16][32] bf16
+  static constexpr int MP_LDS = 2 * WB + 2 * TILEB;
+  static constexpr int RO_LDS = WB + W2B + 2 * TILEB;
+  __device__ static __forceinline__ int apos(int row, int piece) {
+    return row * AROWB + ((piece ^ (row & (PIECES - 1))) << 4);
+  }
+  __device__ static __forceinline__ int wpos(int c, int nb, int j, int lk) {
+    const int row = (c * NB + nb) * 16 + j;      // 64-byte rows of the prepped [chunk][nb][16][32] operand
+    return row * 64 + ((lk ^ swz(row)) << 4);
+  }
+  // this lane's NB channels of a row, in LDS
+  __device__ static __forceinline__ void put(lds_u8 *t, int row, int lr, const float *v) {
+    if constexpr (NB == 8) {
+      v16 q;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
+      st16(t + apos(row, lr), q);
+    } else {
+      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+      *(__attribute__((address_space(3))) u32x2_t *)(t + apos(row, lr >> 1) + 8 * (lr & 1)) =
+          u32x2_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    }
+  }
+};
+constexpr int MP_LDS_BYTES = MlpShape<NRX_D>::MP_LDS;
+constexpr int RO_LDS_BYTES = MlpShape<NRX_D>::RO_LDS;
 
 // Tile sources of the MLP bodies: the layer's tile list strided over the grid, or the
 // MLP_ROWS-row sub-tiles (whole REs) of one larger tile.
@@ -55,29 +77,32 @@ struct SubTiles {
   __device__ int next(int i) const { return i + 1; }
 };
 
-// lds: MP_LDS_BYTES bytes (both weight matrices, then two tile buffers).
-template <int NW, typename Src>
+// lds: MlpShape<W>::MP_LDS bytes (both weight matrices, then two tile buffers).
+template <int NW, int W = NRX_D, typename Src>
 __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src &src, lds_u8 *lds) {
-  using namespace mp2;
+  using Sh = MlpShape<W>;
+  constexpr int NB = Sh::NB, CH = Sh::CH, PIECES = Sh::PIECES, AROWB = Sh::AROWB, TILEB = Sh::TILEB, WB = Sh::WB;
+  auto apos = Sh::apos;
+  auto wpos = Sh::wpos;
   constexpr int MBW = MLP_ROWS / 16 / NW;   // m-blocks per wave
   lds_u8 *lw1 = lds, *lw2 = lds + WB;
   auto lt = [&](int b) { return lds + 2 * WB + b * TILEB; };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int ch0 = 8 * lr;
+  const int ch0 = NB * lr;
   float vmax = 0.f;
   // biases of this lane's channels, read once: a global load inside the tile loop would make the
   // compiler wait for every outstanding vector-memory operation, the next tile's copy included
-  float bias1[8], bias2[8];
+  float bias1[NB], bias2[NB];
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) { bias1[nb] = a.b1[ch0 + nb]; bias2[nb] = a.b2[ch0 + nb]; }
+  for (int nb = 0; nb < NB; ++nb) { bias1[nb] = a.b1[ch0 + nb]; bias2[nb] = a.b2[ch0 + nb]; }
 
   // weights: 2 x 32 KB, 16 DMA instructions of 1 KB per wave (64-byte rows, swizzled pieces)
   {
     const i32x4_t r1 = rsrc_words(a.w1, WB), r2 = rsrc_words(a.w2, WB);
 #pragma unroll
-    for (int j = 0; j < WB / 1024 / NW; ++j) {
+    for (int j = 0; j < (WB / 1024 + NW - 1) / NW; ++j) {
       const int ins = wave + NW * j;
       const int row = ins * 16 + (lane >> 2);
       const uint32_t src = row * 64 + (((lane & 3) ^ swz(row)) << 4);
@@ -88,12 +113,12 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
   // activation tile into buffer b: 32 instructions of 1 KB, 8 per wave; rows past the tile read zero
   auto stage = [&](const Tile &tl, int b) {
     const SlotGeo g = ldc_geo(a.geo + tl.slot);
-    const i32x4_t rs = rsrc_words(a.h + (g.row_base + tl.row0) * NRX_D, tl.nrows * AROWB);
+    const i32x4_t rs = rsrc_words(a.h + (g.row_base + tl.row0) * W, tl.nrows * AROWB);
 #pragma unroll
     for (int j = 0; j < TILEB / 1024 / NW; ++j) {
       const int ins = wave + NW * j;
-      const int row = ins * 4 + (lane >> 4);
-      const int piece = (lane & 15) ^ (row & 15);
+      const int row = ins * (64 / Sh::PIECES) + lane / Sh::PIECES;
+      const int piece = (lane % Sh::PIECES) ^ (row & (Sh::PIECES - 1));
       dma16(rs, lds_addr(lt(b) + ins * 1024), (uint32_t)(row * AROWB + piece * 16));
     }
   };
@@ -108,19 +133,19 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
     const int U = ldc(&a.geo[tl.slot].U);
     lds_u8 *t = lt(b);
     const int rbase = wave * 16 * MBW;
-    f32x4_t acc[MBW][8];
+    f32x4_t acc[MBW][NB];
     auto gemm = [&](const lds_u8 *w) {
 #pragma unroll
       for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < CH; ++c) {
         v16 af[MBW];
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) af[mb] = ld16(t + apos(rbase + mb * 16 + lr, 4 * c + lk));
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
           const v16 bf = ld16(w + wpos(c, nb, lr, lk));
 #pragma unroll
           for (int mb = 0; mb < MBW; ++mb) acc[mb][nb] = mfma_bf16(af[mb], bf, acc[mb][nb]);
@@ -134,41 +159,39 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = rbase + mb * 16 + 4 * lk + i;
-        float v[8];
+        float v[NB];
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
           const float x = acc[mb][nb][i] + bias1[nb];
           v[nb] = x > 0.f ? x : 0.f;
         }
-        v16 q;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
-        st16(t + apos(r, lr), q);
+        Sh::put(t, r, lr, v);
       }
     gemm(lw2);
     auto emit = [&](int r, const float *v) {
       if (r < tl.nrows) {
         const int64_t grow = g.row_base + tl.row0 + r;
-        if (a.out) pack8<bf16_t>::store(a.out + grow * NRX_D + ch0, v);
-        if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * NRX_D + ch0) = fp8x8(v, a.out8_inv);
+        if (a.out) packn<bf16_t, NB>::store(a.out + grow * W + ch0, v);
+        if constexpr (NB == 8)
+          if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * W + ch0) = fp8x8(v, a.out8_inv);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) vmax = fmaxf(vmax, fabsf(v[k]));
+        for (int k = 0; k < NB; ++k) vmax = fmaxf(vmax, fabsf(v[k]));
       }
     };
     if (U != 3) {
       // lane rows 4 lk .. 4 lk + 3 of a 16-row block: whole REs for U = 1, 2, 4
 #pragma unroll
       for (int mb = 0; mb < MBW; ++mb) {
-        float m[4][8];
+        float m[4][NB];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) m[i][nb] = acc[mb][nb][i] + bias2[nb];
+          for (int nb = 0; nb < NB; ++nb) m[i][nb] = acc[mb][nb][i] + bias2[nb];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          float v[8];
+          float v[NB];
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) {
+          for (int nb = 0; nb < NB; ++nb) {
             float tot = 0.f;
 #pragma unroll
             for (int o = 0; o < 4; ++o)
@@ -185,18 +208,15 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
       for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          float v[8];
+          float v[NB];
 #pragma unroll
-          for (int nb = 0; nb < 8; ++nb) v[nb] = acc[mb][nb][i] + bias2[nb];
-          v16 q;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
-          st16(t + apos(rbase + mb * 16 + 4 * lk + i, lr), q);
+          for (int nb = 0; nb < NB; ++nb) v[nb] = acc[mb][nb][i] + bias2[nb];
+          Sh::put(t, rbase + mb * 16 + 4 * lk + i, lr, v);
         }
       __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wave's LDS stores are done
       dma_barrier();
-      for (int e = tid; e < tl.nrows * 16; e += 64 * NW) {
-        const int r = e >> 4, p = e & 15, re0 = r - r % 3;
+      for (int e = tid; e < tl.nrows * PIECES; e += 64 * NW) {
+        const int r = e / PIECES, p = e % PIECES, re0 = r - r % 3;
         float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (int o = 0; o < 3; ++o) {
           if (re0 + o == r) continue;
@@ -206,8 +226,8 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
           for (int k = 0; k < 8; ++k) v[k] += x[k];
         }
         const int64_t grow = g.row_base + tl.row0 + r;
-        if (a.out) pack8<bf16_t>::store(a.out + grow * NRX_D + 8 * p, v);
-        if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * NRX_D + 8 * p) = fp8x8(v, a.out8_inv);
+        if (a.out) pack8<bf16_t>::store(a.out + grow * W + 8 * p, v);
+        if (a.out8) *reinterpret_cast<uint2 *>(a.out8 + grow * W + 8 * p) = fp8x8(v, a.out8_inv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) vmax = fmaxf(vmax, fabsf(v[k]));
       }
@@ -220,47 +240,50 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
 // 128x128 first layer and the 128x16 second layer (outputs j >= m_max zero) are
 // copied to LDS once, 128-row tiles are DMA'd one ahead, and the hidden layer is
 // written back over the wave's own rows.
-// lds: RO_LDS_BYTES bytes (first- and second-layer weights, then two tile buffers).
-template <int NW, typename Src>
+// lds: MlpShape<W>::RO_LDS bytes (first- and second-layer weights, then two tile buffers).
+template <int NW, int W = NRX_D, typename Src>
 __device__ __forceinline__ void readout_lds_body(const MlpArgs<bf16_t> &a, const Src &src, lds_u8 *lds) {
-  using namespace mp2;
+  using Sh = MlpShape<W>;
+  constexpr int NB = Sh::NB, CH = Sh::CH, AROWB = Sh::AROWB, TILEB = Sh::TILEB, WB = Sh::WB, W2B = Sh::W2B;
+  auto apos = Sh::apos;
+  auto wpos = Sh::wpos;
   constexpr int MBW = MLP_ROWS / 16 / NW;   // m-blocks per wave
   lds_u8 *lw1 = lds, *lw2 = lds + WB;
   auto lt = [&](int b) { return lds + WB + W2B + b * TILEB; };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int ch0 = 8 * lr;
+  const int ch0 = NB * lr;
   const int M = a.m_max;
   const int NO = a.n_out ? a.n_out : M;
   const float b2 = lr < NO ? a.b2[lr] : 0.f;
   // first-layer biases of this lane's channels, read once (a global load inside the tile loop
   // would make the compiler wait for every outstanding vector-memory operation, the next
   // tile's copy included)
-  float bias1[8];
+  float bias1[NB];
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) bias1[nb] = a.b1[ch0 + nb];
+  for (int nb = 0; nb < NB; ++nb) bias1[nb] = a.b1[ch0 + nb];
   {
     const i32x4_t r1 = rsrc_words(a.w1, WB), r2 = rsrc_words(a.w2, W2B);
 #pragma unroll
-    for (int j = 0; j < WB / 1024 / NW; ++j) {
+    for (int j = 0; j < (WB / 1024 + NW - 1) / NW; ++j) {
       const int ins = wave + NW * j;
       const int row = ins * 16 + (lane >> 2);
       dma16(r1, lds_addr(&lw1[ins * 1024]), row * 64 + (((lane & 3) ^ swz(row)) << 4));
     }
-    if (wave < 4) {   // 64 rows of 64 bytes: one instruction per wave of the first four
+    if (wave < CH) {   // 16 CH rows of 64 bytes: one instruction per wave of the first CH
       const int row = wave * 16 + (lane >> 2);
       dma16(r2, lds_addr(&lw2[wave * 1024]), row * 64 + (((lane & 3) ^ swz(row)) << 4));
     }
   }
   auto stage = [&](const Tile &tl, int b) {
     const SlotGeo g = ldc_geo(a.geo + tl.slot);
-    const i32x4_t rs = rsrc_words(a.h + (g.row_base + tl.row0) * NRX_D, tl.nrows * AROWB);
+    const i32x4_t rs = rsrc_words(a.h + (g.row_base + tl.row0) * W, tl.nrows * AROWB);
 #pragma unroll
     for (int j = 0; j < TILEB / 1024 / NW; ++j) {
       const int ins = wave + NW * j;
-      const int row = ins * 4 + (lane >> 4);
-      const int piece = (lane & 15) ^ (row & 15);
+      const int row = ins * (64 / Sh::PIECES) + lane / Sh::PIECES;
+      const int piece = (lane % Sh::PIECES) ^ (row & (Sh::PIECES - 1));
       dma16(rs, lds_addr(lt(b) + ins * 1024), (uint32_t)(row * AROWB + piece * 16));
     }
   };
@@ -276,18 +299,18 @@ __device__ __forceinline__ void readout_lds_body(const MlpArgs<bf16_t> &a, const
     const int64_t llr_off = ldc(&a.geo[tl.slot].llr_off);
     lds_u8 *t = lt(b);
     const int rbase = wave * 16 * MBW;
-    f32x4_t acc[MBW][8];
+    f32x4_t acc[MBW][NB];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < CH; ++c) {
       v16 af[MBW];
 #pragma unroll
       for (int mb = 0; mb < MBW; ++mb) af[mb] = ld16(t + apos(rbase + mb * 16 + lr, 4 * c + lk));
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
+      for (int nb = 0; nb < NB; ++nb) {
         const v16 bf = ld16(lw1 + wpos(c, nb, lr, lk));
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) acc[mb][nb] = mfma_bf16(af[mb], bf, acc[mb][nb]);
@@ -297,23 +320,20 @@ __device__ __forceinline__ void readout_lds_body(const MlpArgs<bf16_t> &a, const
     for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float v[8];
+        float v[NB];
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
           const float x = acc[mb][nb][i] + bias1[nb];
           v[nb] = x > 0.f ? x : 0.f;
         }
-        v16 q;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
-        st16(t + apos(rbase + mb * 16 + 4 * lk + i, lr), q);
+        Sh::put(t, rbase + mb * 16 + 4 * lk + i, lr, v);
       }
     // second layer: one 16-column block
     f32x4_t o[MBW];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb) o[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int row = c * 16 + lr;
       const v16 bf = ld16(lw2 + row * 64 + ((lk ^ swz(row)) << 4));
 #pragma unroll
