@@ -91,11 +91,12 @@ struct PrepJob {
   int32_t d_out;       // output columns of the master conv/dense tensor (the state depth d <= 128)
   int32_t seg;         // master input channels per activation segment of width channels (0: identity map)
   int32_t width;       // output columns of the prepped operand (and channels per activation segment): 128 or 64
-  int32_t pad;
+  int32_t unit0;       // first unit (workgroup) of the job
 };
+constexpr int PREP_UNIT = 1024;   // elements of a unit (kinds 0, 1: one K chunk of one tap)
 
 template <typename T>
-void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int64_t total, T *wprep,
+void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int n_units, T *wprep,
                  float *fields, hipStream_t st);
 
 // Front end: DMRS generation, LS pair estimates, interpolation + feature rows.

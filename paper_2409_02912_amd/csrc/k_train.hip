@@ -34,76 +34,104 @@ __device__ __forceinline__ float pe_t_value(int t) {
   return (dist(t) - mean) / sqrtf(var * (1.f / 14.f));
 }
 
+// A workgroup does one unit of a job (found by bisection of the jobs' first units).  The forward operands of
+// convolutions and dense layers (kinds 0, 1) are a transposition: the master's rows are read as they lie, one K
+// chunk of a tap through LDS, and the operand is written as it lies.  The other kinds read contiguously already
+// (transposed operands) or are small, PREP_UNIT elements to a unit.  (One element per thread, each walking the job
+// list and reading a column of its own: 19 us for the 2.2 M weights of the 128-channel network, 51 us for the 89
+// jobs of 8 blocks and 8 rounds at d = 56; now 11 us each.)
 template <typename T>
-__global__ void prep_kernel(const float *w, const PrepJob *jobs, int n_jobs, int64_t total, T *wprep,
-                            float *fields) {
+__global__ __launch_bounds__(256) void prep_kernel(const float *w, const PrepJob *jobs, int n_jobs, T *wprep,
+                                                   float *fields) {
   constexpr int KC = 64 / (int)sizeof(T);
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= total) return;
-  int jb = 0;
-  int64_t base = 0;
-  while (jb < n_jobs && e >= base + jobs[jb].count) { base += jobs[jb].count; ++jb; }
-  const PrepJob J = jobs[jb];
-  const int64_t k = e - base;
-  if (J.kind == 2) {
-    // PE field [par][edge][t][o]
-    const int o = k % NRX_D, t = (k / NRX_D) % 14, edge = (k / (NRX_D * 14)) % 3, par = k / (NRX_D * 42);
-    float acc = 0.f;
-    for (int i = 0; i < 3; ++i) {
-      const int di = i - 1;
-      if ((edge == 1 && di < 0) || (edge == 2 && di > 0)) continue;
-      const float pf = ((par + di) & 1) ? 1.f : -1.f;
-      for (int j = 0; j < 3; ++j) {
-        const int tt = t + j - 1;
-        if (tt < 0 || tt >= 14) continue;
-        if (o >= J.d_out) continue;
-        const int64_t wt = J.src + ((int64_t)(i * 3 + j) * J.cin_total + J.cin_real) * J.d_out + o;
-        acc += w[wt] * pe_t_value(tt) + w[wt + J.d_out] * pf;
-      }
-    }
-    fields[J.dst + k] = acc;
-    return;
+  __shared__ float rows[KC][NRX_D + 1];
+  const int unit = blockIdx.x;
+  int lo = 0, hi = n_jobs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].unit0 <= unit) lo = mid;
+    else hi = mid - 1;
   }
-  if (J.kind == 6) {
-    // bias / LayerNorm vector padded with zeros to 128 channels
-    fields[J.dst + k] = k < J.cin_real ? w[J.src + k] : 0.f;
-    return;
-  }
-  const int kl = k % KC;   // channel within the K chunk (natural order)
-  if (J.kind == 4) {
-    // narrow dense [chunk][16][KC]: column j = output j (zero beyond n_out)
-    const int j = (k / KC) % 16, chunk = k / (16 * KC);
-    const int c = chunk * KC + kl;
-    wprep[J.dst + k] = elem<T>::from_f(j < J.n_out && c < J.cin_real ? w[J.src + (int64_t)c * J.n_out + j] : 0.f);
-    return;
-  }
-  const int nblk = J.width / 16;
-  const int j = (k / KC) % 16, nb = (k / (16 * KC)) % nblk;
-  const int n = nperm(nb, j, nblk);
-  float v = 0.f;
-  if (J.kind == 1) {
-    const int chunk = k / (J.width * KC);
-    const int c = chunk * KC + kl;
-    if (c < J.cin_real && n < J.d_out) v = w[J.src + (int64_t)c * J.d_out + n];
-  } else if (J.kind == 5) {
-    // transposed dense: B[k = c][n] = W[n][c]
-    const int chunk = k / (128 * KC);
-    const int c = chunk * KC + kl;
-    v = w[J.src + (int64_t)n * NRX_D + c];
-  } else {
-    const int tap = (k / (J.width * KC)) % 9, chunk = k / (9 * J.width * KC);
-    const int c = chunk * KC + kl;
-    if (J.kind == 0) {
+  const PrepJob J = jobs[lo];
+  const int ui = unit - J.unit0;
+  if (J.kind <= 1) {
+    // unit: (chunk, tap) of a convolution, chunk of a dense layer; width output columns
+    const int W = J.width, nblk = W / 16;
+    const int chunk = J.kind == 0 ? ui / 9 : ui, tap = J.kind == 0 ? ui - 9 * chunk : 0;
+    const int sh = W == NRX_D ? 7 : 6;   // W is 128 or 64
+    constexpr int NV = KC * NRX_D / 256;
+    float v[NV];                         // all loads before any is used
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = threadIdx.x + 256 * i, kl = e >> sh, n = e & (W - 1), c = chunk * KC + kl;
       // activation channel c -> master input channel (block convs: segments of d of width channels)
-      const int cm = J.seg ? (c / J.width) * J.seg + (c % J.width) : c;
-      const bool in = J.seg ? (c % J.width) < J.seg : true;
-      if (in && cm < J.cin_real && n < J.d_out) v = w[J.src + ((int64_t)tap * J.cin_total + cm) * J.d_out + n];
+      const int cm = J.seg ? (c >> sh) * J.seg + (c & (W - 1)) : c;
+      const bool in = kl < KC && (!J.seg || (c & (W - 1)) < J.seg) && cm < J.cin_real && n < J.d_out;
+      v[i] = in ? w[J.src + ((int64_t)tap * J.cin_total + cm) * J.d_out + n] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = threadIdx.x + 256 * i;
+      if (e >> sh < KC) rows[e >> sh][e & (W - 1)] = v[i];
+    }
+    __syncthreads();
+    T *dst = wprep + J.dst + (int64_t)ui * KC * W;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < KC * W; e += 256) {
+      const int kl = e % KC, j = (e / KC) % 16, nb = e / (16 * KC);
+      dst[e] = elem<T>::from_f(rows[kl][nperm(nb, j, nblk)]);
+    }
+    return;
+  }
+  float *pt = &rows[0][0];   // positional encoding of the 14 symbols (kind 2)
+  if (J.kind == 2) {
+    if (threadIdx.x < 14) pt[threadIdx.x] = pe_t_value(threadIdx.x);
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < PREP_UNIT; i += 256) {
+    const int64_t k = (int64_t)ui * PREP_UNIT + i;
+    if (k >= J.count) return;
+    if (J.kind == 2) {
+      // PE field [par][edge][t][o]
+      const int o = k % NRX_D, t = (k / NRX_D) % 14, edge = (k / (NRX_D * 14)) % 3, par = k / (NRX_D * 42);
+      float acc = 0.f;
+      for (int r = 0; r < 3; ++r) {
+        const int di = r - 1;
+        if ((edge == 1 && di < 0) || (edge == 2 && di > 0)) continue;
+        const float pf = ((par + di) & 1) ? 1.f : -1.f;
+        for (int j = 0; j < 3; ++j) {
+          const int tt = t + j - 1;
+          if (tt < 0 || tt >= 14) continue;
+          if (o >= J.d_out) continue;
+          const int64_t wt = J.src + ((int64_t)(r * 3 + j) * J.cin_total + J.cin_real) * J.d_out + o;
+          acc += w[wt] * pt[tt] + w[wt + J.d_out] * pf;
+        }
+      }
+      fields[J.dst + k] = acc;
+    } else if (J.kind == 6) {
+      // bias / LayerNorm vector padded with zeros to 128 channels
+      fields[J.dst + k] = k < J.cin_real ? w[J.src + k] : 0.f;
     } else {
-      // transposed, flipped: K = original output channel c, N = original input channel cin_first + n
-      v = w[J.src + ((int64_t)(8 - tap) * J.cin_total + J.cin_first + n) * NRX_D + c];
+      const int kl = k % KC;   // channel within the K chunk (natural order)
+      float v = 0.f;
+      if (J.kind == 4) {
+        // narrow dense [chunk][16][KC]: column j = output j (zero beyond n_out)
+        const int j = (k / KC) % 16, c = (int)(k / (16 * KC)) * KC + kl;
+        if (j < J.n_out && c < J.cin_real) v = w[J.src + (int64_t)c * J.n_out + j];
+      } else {
+        const int j = (k / KC) % 16, nb = (k / (16 * KC)) % 8, n = nperm(nb, j);
+        if (J.kind == 5) {
+          // transposed dense: B[k = c][n] = W[n][c]
+          v = w[J.src + (int64_t)n * NRX_D + (int)(k / (128 * KC)) * KC + kl];
+        } else {
+          // transposed, flipped: K = original output channel c, N = original input channel cin_first + n
+          const int tap = (k / (128 * KC)) % 9, c = (int)(k / (1152 * KC)) * KC + kl;
+          v = w[J.src + ((int64_t)(8 - tap) * J.cin_total + J.cin_first + n) * NRX_D + c];
+        }
+      }
+      wprep[J.dst + k] = elem<T>::from_f(v);
     }
   }
-  wprep[J.dst + k] = elem<T>::from_f(v);
 }
 
 __global__ void bce_kernel(const SlotGeo *geo, int m_max, const float *llr, const uint8_t *bits, float *dllr,
@@ -215,13 +243,12 @@ __global__ void adam_kernel(float *w, const float *g, float *m, float *v, int64_
 }  // namespace
 
 template <typename T>
-void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int64_t total, T *wprep, float *fields,
+void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int n_units, T *wprep, float *fields,
                  hipStream_t st) {
-  hipLaunchKernelGGL(prep_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, jobs, n_jobs, total,
-                     wprep, fields);
+  hipLaunchKernelGGL(prep_kernel<T>, dim3(n_units), dim3(256), 0, st, w, jobs, n_jobs, wprep, fields);
 }
-template void launch_prep<float>(const float *, const PrepJob *, int, int64_t, float *, float *, hipStream_t);
-template void launch_prep<bf16_t>(const float *, const PrepJob *, int, int64_t, bf16_t *, float *, hipStream_t);
+template void launch_prep<float>(const float *, const PrepJob *, int, int, float *, float *, hipStream_t);
+template void launch_prep<bf16_t>(const float *, const PrepJob *, int, int, bf16_t *, float *, hipStream_t);
 
 void launch_bce(const SlotGeo *geo, const int64_t *, int n_slots, int64_t max_ute, int m_max, const float *llr,
                 const uint8_t *bits, float *dllr, double *partials, int n_part_per_slot, double *loss,

@@ -471,7 +471,8 @@ struct nrx_model {
   bool chest = false;                   // flags bit 1: second readout ReadoutChEst (double readout)
   DenseLayer ro_ch;
   std::vector<PrepJob> jobs;
-  int64_t prep_elems = 0, field_elems = 0, prep_total = 0;
+  int64_t prep_elems = 0, field_elems = 0;
+  int prep_units = 0, bprep_units = 0;   // workgroups of the preparation kernel
   void *pinned_jobs = nullptr;
   std::vector<PrepJob> bjobs;           // backward weight preparation
   int64_t bprep_elems = 0;
@@ -734,9 +735,17 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
       m->field_elems += NRX_D;
     }
   }
-  // field jobs index a separate buffer; the prep kernel walks jobs in order over one index space
-  m->prep_total = 0;
-  for (auto &j : m->jobs) m->prep_total += j.count;
+  // units (workgroups) of the preparation kernel, job after job
+  auto count_units = [&](std::vector<PrepJob> &jobs) {
+    int u = 0;
+    for (auto &j : jobs) {
+      j.unit0 = u;
+      u += j.kind == 0 ? 9 * j.n_chunks : (j.kind == 1 ? j.n_chunks : (int)((j.count + PREP_UNIT - 1) / PREP_UNIT));
+    }
+    return u;
+  };
+  m->prep_units = count_units(m->jobs);
+  m->bprep_units = count_units(m->bjobs);
   *out = m.release();
   return NRX_OK;
 }
@@ -982,7 +991,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
   launch_stamp_start((unsigned int *)(ws + L.done), (unsigned long long *)(ws + L.stamps), slot_flags, P->n, st);
   {
     ProfMark pm(m, NRX_K_FRONTEND, st);
-    launch_prep<T>(w, (const PrepJob *)(ws + L.jobs), (int)m->jobs.size(), m->prep_total, wprep, fields, st);
+    launch_prep<T>(w, (const PrepJob *)(ws + L.jobs), (int)m->jobs.size(), m->prep_units, wprep, fields, st);
     launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st);
     launch_features<T>(D.geo, P->n, P->max_rows, (const float2 *)y, pairs, D.pair_off, m->cfg.n_ant, m->cx, X,
                        (float2 *)h_ls, st, slot_flags);
@@ -1665,7 +1674,7 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
   HIPCHK(hipMemcpyAsync(ws + L.bjobs, m->pinned_bjobs, sizeof(PrepJob) * m->bjobs.size(), hipMemcpyHostToDevice, st));
   const Dev D = dev_tables(P, ws + L.meta);
   T *bp = (T *)(ws + L.bprep);
-  launch_prep<T>(w, (const PrepJob *)(ws + L.bjobs), (int)m->bjobs.size(), m->bprep_elems, bp, nullptr, st);
+  launch_prep<T>(w, (const PrepJob *)(ws + L.bjobs), (int)m->bjobs.size(), m->bprep_units, bp, nullptr, st);
   HIPCHK(hipMemsetAsync(ws + L.zero, 0, 128 * 4, st));
   auto buf = [&](size_t off) { return (T *)(ws + off); };
   const float *zero = (const float *)(ws + L.zero);
