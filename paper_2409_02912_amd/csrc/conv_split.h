@@ -1,0 +1,222 @@
+// FP32 3x3 convolution on the BF16 matrix cores: every operand as the sum of three BF16 numbers.
+//
+// A float has 24 significant bits, a BF16 number 8: x = h + m + l with h = bf16(x), m = bf16(x - h),
+// l = bf16(x - h - m) is exact (round to nearest: |m| <= 2^-9 |x|, |l| <= 2^-18 |x|).  A product of two floats is
+// then nine products of BF16 numbers, exact in FP32; the six largest are taken (h h, h m, m h, m m, h l, l h), what
+// is left out is at most 2^-26 of the product, a quarter of the rounding of one FP32 addition.  Six BF16 products
+// of 32 channels take 96 clocks of the matrix core against 256 for the FP32 ones, and an accumulator is rounded
+// three times per 16 channels instead of sixteen times: against 64 bits the result is nearer than the FP32 kernels'.
+//
+// The six go in pairs of 16 channels through 32-deep MFMAs: lanes of the lower K half take one term, those of the
+// upper half another.  Weights are split when they are prepared, in two 64-byte rows per (16 channels, column),
+// [h | m] and [l | h]; activations stay FP32 in memory and are split in registers (A is h, m, and h in the lower,
+// l in the upper half), each fragment once for the eight column blocks of a tap.
+//
+// The pipeline is that of conv_pipe_body with one tap (24 MFMAs of 16 clocks per row block) to a group: three weight
+// slots of one tap; the next tap's activations and its first weight fragments are read before the barrier.
+// Values that are not finite give NaN where FP32 products would give an infinity; these convolutions feed a
+// LayerNorm, which makes NaN of either, or take its output, which is finite.
+//
+// 128 -> 128 channels, 366,912 rows: 0.87 -> 0.60 ms (180 TFLOP/s of FP32; the FP32 products reach 124 here and 154
+// in a library product of 8192^3); 4 slots x 273 PRB, 6 blocks: 13.07 -> 8.87 ms, distance from 64 bits 8.9e-7 ->
+// 8.6e-7.
+#pragma once
+#include "conv_common.h"
+#include "conv_ring.h"
+
+namespace {
+
+constexpr int SPLIT_SET = 8 * 16 * ROWB;        // one set of weight rows of a tap ([h | m] or [l | h])
+constexpr int SPLIT_TAP = 2 * SPLIT_SET;        // a tap of a 16-channel chunk
+constexpr int SPLIT_SLOTS = 3;
+
+template <int MB, int NW>
+struct SplitShape : PipeShape<MB, NW> {
+  static constexpr int LDS_BYTES = 2 * PipeShape<MB, NW>::ABYTES + SPLIT_SLOTS * SPLIT_TAP;
+};
+
+// the three BF16 parts of 8 floats, packed in pairs
+struct Split8 {
+  v16 h, m, l;
+};
+__device__ __forceinline__ Split8 split8(const v16 &x0, const v16 &x1) {
+  Split8 s;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float a = __uint_as_float(k < 2 ? x0.w[2 * k] : x1.w[2 * k - 4]);
+    float b = __uint_as_float(k < 2 ? x0.w[2 * k + 1] : x1.w[2 * k - 3]);
+    s.h.w[k] = pack_bf2(a, b);
+    a -= __uint_as_float(s.h.w[k] << 16);
+    b -= __uint_as_float(s.h.w[k] & 0xFFFF0000u);
+    s.m.w[k] = pack_bf2(a, b);
+    a -= __uint_as_float(s.m.w[k] << 16);
+    b -= __uint_as_float(s.m.w[k] & 0xFFFF0000u);
+    s.l.w[k] = pack_bf2(a, b);
+  }
+  return s;
+}
+
+template <int EPI, int MB, int NW, typename Src>
+__device__ __forceinline__ void conv_split_body(const ConvArgs<float> &a, const Src &src, lds_u8 *lds) {
+  using Sh = SplitShape<MB, NW>;
+  constexpr int APW = Sh::APW, ZROW = Sh::ZROW, KC = 16;
+  constexpr int BPW = SPLIT_TAP / 1024 / NW;       // weight copies per wave and tap
+  static_assert(SPLIT_TAP / 1024 % NW == 0 && APW < 16, "shape");
+  constexpr int WAIT_KEEP_A = (0xF << 8) | (7 << 4) | APW;
+  auto lds_a = [&](int b) { return lds + b * Sh::ABYTES; };
+  lds_u8 *lds_b = lds + 2 * Sh::ABYTES;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  if (tid < 4) {
+    v16 z = {{0, 0, 0, 0}};
+    st16(lds_a(0) + ZROW * ROWB + tid * 16, z);
+    st16(lds_a(1) + ZROW * ROWB + tid * 16, z);
+  }
+  const int nch = (a.c0 + a.c1) / KC, ntap = 9 * nch;
+  const i32x4_t wrs = rsrc_words(a.wsplit, 0x7FFFFFFF);
+  const uint32_t wlane = (uint32_t)((lane >> 2) * ROWB + (((lane & 3) ^ swz(lane >> 2)) << 4));
+  auto stage_tap = [&](int tap, int slot) {
+#pragma unroll
+    for (int j = 0; j < BPW; ++j) {
+      const int ins = wave + NW * j;
+      dma16(wrs, lds_addr(lds_b + slot * SPLIT_TAP + ins * 1024), wlane + (uint32_t)(tap * SPLIT_TAP + ins * 1024));
+    }
+  };
+  struct Geo {
+    int64_t row_base;
+    int rel0, halo, S, rps, U;
+  };
+  auto geo_of = [&](const Tile &tl) {
+    const SlotGeo g = ldc_geo(a.geo + tl.slot);
+    Geo q;
+    q.U = g.U;
+    q.S = g.S;
+    q.rps = 14 * g.U;
+    const int s_first = tl.row0 / q.rps;
+    const int s_last = (tl.row0 + tl.nrows - 1) / q.rps;
+    q.halo = (s_last - s_first + 3) * q.rps;
+    q.rel0 = (s_first - 1) * q.rps;
+    q.row_base = g.row_base;
+    return q;
+  };
+  auto stage_a = [&](const Geo &q, int c, int b) {
+    const float *srcp;
+    int cs, coff;
+    if (c * KC < a.c0) { srcp = a.src0; cs = a.c0; coff = c * KC; }
+    else { srcp = a.src1; cs = a.c1; coff = c * KC - a.c0; }
+    const i32x4_t rs = rsrc_words(srcp + q.row_base * cs + coff, q.S * q.rps * cs * 4);
+#pragma unroll
+    for (int j = 0; j < APW; ++j) {
+      const int ins = wave + NW * j;
+      const int h = ins * 16 + (lane >> 2);
+      const int piece = (lane & 3) ^ swz(h);
+      const uint32_t voff = h < q.halo ? (uint32_t)((q.rel0 + h) * cs * 4 + piece * 16) : 0x80000000u;
+      dma16(rs, lds_addr(lds_a(b) + ins * 16 * ROWB), voff);
+    }
+  };
+
+  int ka = 0, rd = 0;   // halo buffer, slot of the current tap
+  int tile = src.first;
+  if (src.valid(tile)) {
+    stage_tap(0, 0);
+    stage_tap(1, 1);
+    stage_a(geo_of(src.get(tile)), 0, 0);
+    __builtin_amdgcn_s_waitcnt(0);
+    dma_barrier();
+  }
+  const int blane = lr * ROWB + ((lk ^ swz(lr)) << 4);
+  const int p0 = 2 * (lk & 1);   // this lane's 8 channels of a 16-channel row: pieces p0, p0 + 1
+  for (; src.valid(tile); tile = src.next(tile)) {
+    const Tile tl = src.get(tile);
+    const Geo q = geo_of(tl);
+    int hc[MB], tt[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int r = wave * 16 * MB + mb * 16 + lr;
+      const int R = tl.row0 + r;
+      const int s = R / q.rps;
+      tt[mb] = r < tl.nrows ? (R - s * q.rps) / q.U : -1;
+      hc[mb] = R - q.rel0;
+    }
+    f32x4_t acc[MB][8];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    v16 raw[MB][2], ah[MB], am[MB], ax[MB];
+    auto load_a = [&](const lds_u8 *la, int di, int dj) {
+      const int off = di * q.rps + dj * q.U;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const bool ok = tt[mb] >= 0 && (dj >= 0 || tt[mb] > 0) && (dj <= 0 || tt[mb] < 13);
+        const int row = ok ? hc[mb] + off : ZROW;
+        const int sw = swz(row);
+        raw[mb][0] = ld16(la + row * ROWB + ((p0 ^ sw) << 4));
+        raw[mb][1] = ld16(la + row * ROWB + (((p0 + 1) ^ sw) << 4));
+      }
+    };
+    auto split = [&](int mb) {
+      const Split8 s = split8(raw[mb][0], raw[mb][1]);
+      ah[mb] = s.h;
+      am[mb] = s.m;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ax[mb].w[k] = lk < 2 ? s.h.w[k] : s.l.w[k];
+    };
+    const int next_tile = src.next(tile);
+    const bool has_next = src.valid(next_tile);
+    load_a(lds_a(ka & 1), -1, -1);
+    v16 b0 = ld16(lds_b + rd * SPLIT_TAP + blane), b1 = ld16(lds_b + rd * SPLIT_TAP + SPLIT_SET + blane);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) split(mb);
+    int tap = 0, c = 0;
+#pragma unroll 1
+    for (int k = 0; k < ntap; ++k) {
+      bool halo = false;
+      const int nxt = rd + 1 == SPLIT_SLOTS ? 0 : rd + 1, req = nxt + 1 == SPLIT_SLOTS ? 0 : nxt + 1;
+      stage_tap(k + 2 < ntap ? k + 2 : k + 2 - ntap, req);
+      if (tap == 0) {
+        if (c + 1 < nch) { stage_a(q, c + 1, (ka + 1) & 1); halo = true; }
+        else if (has_next) { stage_a(geo_of(src.get(next_tile)), 0, (ka + 1) & 1); halo = true; }
+      }
+      const int tap_n = tap == 8 ? 0 : tap + 1;
+      const lds_u8 *la_next = lds_a((tap == 8 ? ka + 1 : ka) & 1);
+      const lds_u8 *lb = lds_b + rd * SPLIT_TAP + blane, *lb_next = lds_b + nxt * SPLIT_TAP + blane;
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) {
+        if (nb == 0) __builtin_amdgcn_s_setprio(3);
+        else if (nb == 2) __builtin_amdgcn_s_setprio(2);
+        else if (nb == 4) __builtin_amdgcn_s_setprio(1);
+        else if (nb == 6) __builtin_amdgcn_s_setprio(0);
+        const lds_u8 *ln = nb < 7 ? lb + (nb + 1) * 1024 : lb_next;
+        const v16 n0 = ld16(ln), n1 = ld16(ln + SPLIT_SET);
+        if (nb == 3) load_a(la_next, tap_n / 3 - 1, tap_n % 3 - 1);
+        // the small terms first
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = mfma_bf16(ax[mb], b1, acc[mb][nb]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = mfma_bf16(am[mb], b0, acc[mb][nb]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          acc[mb][nb] = mfma_bf16(ah[mb], b0, acc[mb][nb]);
+          if (nb == 7) split(mb);   // the next tap's, after the last use of this one's
+        }
+        b0 = n0;
+        b1 = n1;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (halo) __builtin_amdgcn_s_waitcnt(WAIT_KEEP_A);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) alone
+      dma_barrier();
+      rd = nxt;
+      if (tap == 8) { ka += 1; c += 1; }
+      tap = tap_n;
+    }
+    conv_epilogue<float, MB, EPI>(a, tl, ldc_geo(a.geo + tl.slot), acc, wave, lr, lk, nullptr);
+  }
+  __builtin_amdgcn_s_waitcnt(0);   // no copy into LDS outlives the call
+}
+
+}  // namespace

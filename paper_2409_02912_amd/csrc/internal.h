@@ -13,6 +13,7 @@ struct ConvArgs {
   const T *src1;            // [rows][c1] or null (channel concatenation)
   int c0, c1;
   const T *w;               // prepped [chunk][tap][nb][16][KC]
+  const void *wsplit;       // FP32 by BF16 parts (conv3x3_split_kernel): prepped [chunk][tap][2][nb][16][64 B], or null
   const float *bias;        // [128]
   const float *pe;          // positional-encoding field [2][3][14][128] or null
   const float *ln_g, *ln_b; // [128] (EPI_LN_RELU; zero beyond the state depth d)
@@ -76,10 +77,14 @@ void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, h
 // BF16 inference of networks with d <= 64: rows of 64 channels, tiles of 128 mb rows.
 void launch_conv_narrow(const ConvArgs<bf16_t> &a, int epi, int mb, int grid, hipStream_t st);
 
+// FP32 by BF16 parts: EPI_LN_RELU, EPI_RESID, EPI_LN_RELU_SAVE; operands a.wsplit, tiles of 128 mb rows.
+void launch_conv_split(const ConvArgs<float> &a, int epi, int mb, int grid, hipStream_t st);
+
 // Weight preparation: fp32 master -> MFMA operand layouts and PE fields.
 struct PrepJob {
   int32_t kind;        // 0 conv, 1 dense, 2 PE field, 3 conv transposed+flipped (dgrad), 4 narrow dense,
-                       // 5 dense transposed, 6 vector zero-padded to 128 (into the field buffer)
+                       // 5 dense transposed, 6 vector zero-padded to 128 (into the field buffer),
+                       // 7 conv in BF16 parts (FP32 models)
   int32_t cin_real;    // input channels present in the master tensor (conv: without PE)
   int32_t cin_total;   // input channels of the master tensor (incl. PE channels)
   int32_t n_chunks;    // K chunks of the prepped operand
@@ -93,11 +98,12 @@ struct PrepJob {
   int32_t width;       // output columns of the prepped operand (and channels per activation segment): 128 or 64
   int32_t unit0;       // first unit (workgroup) of the job
 };
-constexpr int PREP_UNIT = 1024;   // elements of a unit (kinds 0, 1: one K chunk of one tap)
+constexpr int PREP_UNIT = 1024;   // elements of a unit (kinds 0, 1, 7: one K chunk of one tap)
+enum { PREP_SKIP_BLOCKS = 1, PREP_SKIP_SPLIT = 2 };   // operands no launch will read: kind 0 of block convs, kind 7
 
 template <typename T>
 void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int n_units, T *wprep,
-                 float *fields, hipStream_t st);
+                 float *fields, hipStream_t st, int skip = 0);
 
 // Front end: DMRS generation, LS pair estimates, interpolation + feature rows.
 // slot_mask (nullable, device, one word per slot): when given, slots whose word is 0 are skipped.

@@ -29,6 +29,7 @@
 #include "internal.h"
 #include "conv_common.h"
 #include "conv_ring.h"
+#include "conv_split.h"
 
 #ifndef NRX_LDS_MB
 #define NRX_LDS_MB 6
@@ -400,6 +401,12 @@ __global__ __launch_bounds__(512, 1) void conv3x3_narrow_kernel(ConvArgs<bf16_t>
   conv_pipe_body<bf16_t, EPI, MB, 8, 4>(a, GridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds, lnp);
 }
 
+template <int EPI, int MB>
+__global__ __launch_bounds__(512, 1) void conv3x3_split_kernel(ConvArgs<float> a) {
+  __shared__ __align__(16) unsigned char lds[SplitShape<MB, 8>::LDS_BYTES];
+  conv_split_body<EPI, MB, 8>(a, GridTiles(a.tiles, a.n_tiles), (lds_u8 *)lds);
+}
+
 }  // namespace
 
 // Compiled shapes: rows per wave (16*MB), waves per SIMD, B-operand prefetch.
@@ -490,6 +497,19 @@ void launch_conv(const ConvArgs<T> &a, int epi, int variant, int mb, int grid, h
   if (mb == 2) NRX_RING_CASE(14, 2, 8, 3, 1, 7, 4, 0, 0)
   NRX_RING_CASE(14, 1, 8, 3, 1, 7, 4, 0, 0)
 #undef NRX_RING_CASE
+}
+
+void launch_conv_split(const ConvArgs<float> &a, int epi, int mb, int grid, hipStream_t st) {
+  auto run = [&](auto ln, auto resid, auto save) {
+    auto k = epi == EPI_LN_RELU ? ln : (epi == EPI_RESID ? resid : save);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, a);
+  };
+#define NRX_SPLIT(M) \
+  run(conv3x3_split_kernel<EPI_LN_RELU, M>, conv3x3_split_kernel<EPI_RESID, M>, conv3x3_split_kernel<EPI_LN_RELU_SAVE, M>)
+  if (mb == 3) NRX_SPLIT(3);
+  else if (mb == 2) NRX_SPLIT(2);
+  else NRX_SPLIT(1);
+#undef NRX_SPLIT
 }
 
 void launch_conv_narrow(const ConvArgs<bf16_t> &a, int epi, int mb, int grid, hipStream_t st) {

@@ -42,7 +42,7 @@ __device__ __forceinline__ float pe_t_value(int t) {
 // jobs of 8 blocks and 8 rounds at d = 56; now 11 us each.)
 template <typename T>
 __global__ __launch_bounds__(256) void prep_kernel(const float *w, const PrepJob *jobs, int n_jobs, T *wprep,
-                                                   float *fields) {
+                                                   float *fields, int skip) {
   constexpr int KC = 64 / (int)sizeof(T);
   __shared__ float rows[KC][NRX_D + 1];
   const int unit = blockIdx.x;
@@ -54,10 +54,11 @@ __global__ __launch_bounds__(256) void prep_kernel(const float *w, const PrepJob
   }
   const PrepJob J = jobs[lo];
   const int ui = unit - J.unit0;
-  if (J.kind <= 1) {
+  if ((J.kind == 0 && J.seg && (skip & PREP_SKIP_BLOCKS)) || (J.kind == 7 && (skip & PREP_SKIP_SPLIT))) return;
+  if (J.kind <= 1 || J.kind == 7) {
     // unit: (chunk, tap) of a convolution, chunk of a dense layer; width output columns
     const int W = J.width, nblk = W / 16;
-    const int chunk = J.kind == 0 ? ui / 9 : ui, tap = J.kind == 0 ? ui - 9 * chunk : 0;
+    const int chunk = J.kind != 1 ? ui / 9 : ui, tap = J.kind != 1 ? ui - 9 * chunk : 0;
     const int sh = W == NRX_D ? 7 : 6;   // W is 128 or 64
     constexpr int NV = KC * NRX_D / 256;
     float v[NV];                         // all loads before any is used
@@ -75,6 +76,26 @@ __global__ __launch_bounds__(256) void prep_kernel(const float *w, const PrepJob
       if (e >> sh < KC) rows[e >> sh][e & (W - 1)] = v[i];
     }
     __syncthreads();
+    if constexpr (sizeof(T) == 4) {
+      if (J.kind == 7) {
+        // two sets of 64-byte rows [nb][16]: [h | m] and [l | h] of the chunk's 16 channels in BF16
+        uint32_t *dst = reinterpret_cast<uint32_t *>(wprep + J.dst) + (int64_t)ui * 4096;
+        for (int e = threadIdx.x; e < 4096; e += 256) {
+          const int set = e >> 11, nb = (e >> 8) & 7, j = (e >> 4) & 15, wd = e & 15;
+          const int kl = 2 * (wd & 7), n = nperm(nb, j);
+          float x0 = rows[kl][n], x1 = rows[kl + 1][n];
+          uint32_t part[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            part[k] = pack_bf2(x0, x1);
+            x0 -= __uint_as_float(part[k] << 16);
+            x1 -= __uint_as_float(part[k] & 0xFFFF0000u);
+          }
+          dst[e] = set ? (wd < 8 ? part[2] : part[0]) : (wd < 8 ? part[0] : part[1]);
+        }
+        return;
+      }
+    }
     T *dst = wprep + J.dst + (int64_t)ui * KC * W;
 #pragma unroll 4
     for (int e = threadIdx.x; e < KC * W; e += 256) {
@@ -244,11 +265,11 @@ __global__ void adam_kernel(float *w, const float *g, float *m, float *v, int64_
 
 template <typename T>
 void launch_prep(const float *w, const PrepJob *jobs, int n_jobs, int n_units, T *wprep, float *fields,
-                 hipStream_t st) {
-  hipLaunchKernelGGL(prep_kernel<T>, dim3(n_units), dim3(256), 0, st, w, jobs, n_jobs, wprep, fields);
+                 hipStream_t st, int skip) {
+  hipLaunchKernelGGL(prep_kernel<T>, dim3(n_units), dim3(256), 0, st, w, jobs, n_jobs, wprep, fields, skip);
 }
-template void launch_prep<float>(const float *, const PrepJob *, int, int, float *, float *, hipStream_t);
-template void launch_prep<bf16_t>(const float *, const PrepJob *, int, int, bf16_t *, float *, hipStream_t);
+template void launch_prep<float>(const float *, const PrepJob *, int, int, float *, float *, hipStream_t, int);
+template void launch_prep<bf16_t>(const float *, const PrepJob *, int, int, bf16_t *, float *, hipStream_t, int);
 
 void launch_bce(const SlotGeo *geo, const int64_t *, int n_slots, int64_t max_ute, int m_max, const float *llr,
                 const uint8_t *bits, float *dllr, double *partials, int n_part_per_slot, double *loss,

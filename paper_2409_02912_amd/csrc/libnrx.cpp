@@ -77,6 +77,8 @@ int conv_mb(const std::vector<Tile> *ct, double over, int max_mb) {
   return best;
 }
 constexpr double CONV_OVER_NARROW = 5.0;   // 64-channel rows: a tap's weights, not its products, are most of a round
+constexpr double CONV_OVER_SPLIT = 0.3;    // FP32 by BF16 parts
+constexpr int CONV_SPLIT_MB = 3;           // (512-row tiles would spill the parts of their fragments)
 template <typename T>
 constexpr double conv_over = sizeof(T) == 2 ? 0.8 : 0.17;
 inline int variant_tiles(const ConvVariant &v) { return v.aligned ? ALIGNED_TILES : tile_size_index(v.mb); }
@@ -93,6 +95,7 @@ struct ConvLayer {
   int cin_real = 0, cin_total = 0, n_chunks = 0;
   int64_t prep = 0;             // element offset in the prepped buffer
   int64_t field = -1;           // element offset in the field buffer (PE folded) or -1
+  int64_t split = -1;           // FP32 models, block convs: element offset of the operand in BF16 parts
   int64_t w8 = -1, ws8 = -1;    // FP8 models: byte offset of the E4M3 operand, float offset of its scales
   int64_t bpad = -1;            // d < 128: bias padded to 128 channels (field buffer offset)
 };
@@ -623,6 +626,12 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
     PrepJob j{0, cin_real, cin_total, L.n_chunks, 0, 0, w, L.prep, (int64_t)cin_pad * 9 * m->width, d, seg, m->width, 0};
     m->jobs.push_back(j);
     m->prep_elems += j.count;
+    if (c.precision == NRX_FP32 && seg) {
+      L.split = m->prep_elems;
+      m->jobs.push_back(PrepJob{7, cin_real, cin_total, L.n_chunks, 0, 0, w, L.split, (int64_t)L.n_chunks * 9 * 4096, d, seg,
+                                NRX_D, 0});
+      m->prep_elems += m->jobs.back().count;
+    }
     if (pe) {
       L.field = m->field_elems;
       PrepJob f{2, cin_real, cin_total, 0, 0, 0, w, L.field, 2 * 3 * 14 * 128, d, 0, NRX_D, 0};
@@ -740,7 +749,7 @@ extern "C" nrx_status nrx_model_create(const nrx_model_config *cfg, nrx_model **
     int u = 0;
     for (auto &j : jobs) {
       j.unit0 = u;
-      u += j.kind == 0 ? 9 * j.n_chunks : (j.kind == 1 ? j.n_chunks : (int)((j.count + PREP_UNIT - 1) / PREP_UNIT));
+      u += j.kind == 0 || j.kind == 7 ? 9 * j.n_chunks : (j.kind == 1 ? j.n_chunks : (int)((j.count + PREP_UNIT - 1) / PREP_UNIT));
     }
     return u;
   };
@@ -989,9 +998,16 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
   T *X = (T *)(ws + L.X);
   unsigned int *slot_flags = (unsigned int *)(ws + L.flags);
   launch_stamp_start((unsigned int *)(ws + L.done), (unsigned long long *)(ws + L.stamps), slot_flags, P->n, st);
+  // FP32 block convs of the default variant run on BF16 parts, the others on FP32 operands: prepare what is read
+  int prep_skip = 0;
+  if (std::is_same<T, float>::value) {
+    prep_skip = PREP_SKIP_BLOCKS | PREP_SKIP_SPLIT;
+    for (int cls : {NRX_K_CONV_A, NRX_K_CONV_A_MP, NRX_K_CONV_B})
+      prep_skip &= m->conv_variant[cls] == CONV_DEFAULT_VARIANT ? ~PREP_SKIP_SPLIT : ~PREP_SKIP_BLOCKS;
+  }
   {
     ProfMark pm(m, NRX_K_FRONTEND, st);
-    launch_prep<T>(w, (const PrepJob *)(ws + L.jobs), (int)m->jobs.size(), m->prep_units, wprep, fields, st);
+    launch_prep<T>(w, (const PrepJob *)(ws + L.jobs), (int)m->jobs.size(), m->prep_units, wprep, fields, st, prep_skip);
     launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st);
     launch_features<T>(D.geo, P->n, P->max_rows, (const float2 *)y, pairs, D.pair_off, m->cfg.n_ant, m->cx, X,
                        (float2 *)h_ls, st, slot_flags);
@@ -1050,6 +1066,16 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       }
     }
     int v = m->conv_variant[cls];
+    if constexpr (std::is_same<T, float>::value) {
+      if (v == CONV_DEFAULT_VARIANT && ca.wsplit) {
+        const int mb = conv_mb(P->ct, CONV_OVER_SPLIT, CONV_SPLIT_MB);
+        ca.tiles = D.ct[mb - 1];
+        ca.n_tiles = (int)P->ct[mb - 1].size();
+        ProfMark pm(m, cls, st);
+        launch_conv_split(ca, epi, mb, (std::min(ca.n_tiles, num_cu()) + 7) / 8 * 8, st);
+        return;
+      }
+    }
     if (fp8op) v = std::min(v, NRX_CONV8_VARIANTS - 1);
     else if (m->fp8 && cls != NRX_K_CONV_IN) v = CONV_DEFAULT_VARIANT;   // a block conv kept in BF16
     else if (kConvVariants[v].pref == 2 && ((ca.c0 + ca.c1) / (64 / (int)sizeof(T))) % 2)
@@ -1196,6 +1222,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     ca.src0 = h_in; ca.c0 = m->width;
     ca.src1 = agg; ca.c1 = agg ? m->width : 0;
     ca.w = wprep + B.a.prep;
+    ca.wsplit = B.a.split >= 0 ? wprep + B.a.split : nullptr;
     ca.bias = vec(B.a.b, B.a.bpad);
     ca.pe = B.a.field >= 0 ? fields + B.a.field : nullptr;
     ca.ln_g = vec(B.g, B.gpad);
@@ -1219,6 +1246,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     ConvArgs<T> cb = a;
     cb.src0 = abuf; cb.c0 = m->width; cb.src1 = nullptr; cb.c1 = 0;
     cb.w = wprep + B.b.prep;
+    cb.wsplit = B.b.split >= 0 ? wprep + B.b.split : nullptr;
     cb.bias = vec(B.b.b, B.b.bpad);
     cb.pe = nullptr;
     cb.resid = h_in;

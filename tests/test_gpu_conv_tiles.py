@@ -1,5 +1,7 @@
 """The default convolution picks its tile (128 to 512 rows) by the number of rows of a launch.  Whatever the tile, an
-output is the same products accumulated in the same order: the LLRs equal those of a fixed-tile variant bit for bit.
+output is the same products accumulated in the same order: BF16 LLRs equal those of a fixed-tile variant bit for bit.
+FP32 models run their block convolutions on three BF16 parts per operand there, exact products with fewer roundings than
+the FP32 variant: the two agree to 1e-5 (each is about 1e-6 from 64 bits after two blocks).
 The training epilogues add their LayerNorm gradients up per tile, so a batch of n copies of one slot must give n times
 that slot's gradient up to the rounding of the sums: fp32 partial sums of at most 512 rows x a few hundred workgroups,
 each addition 6e-8 relative, random in sign, far below 1e-5 of the gradient's norm."""
@@ -45,7 +47,10 @@ def test_tile_rule_keeps_every_bit(size, prec):
             torch.cuda.synchronize()
             out.append(llr)
         assert torch.isfinite(out[0]).all()
-        assert torch.equal(out[0], out[1])
+        if prec == 1:
+            assert torch.equal(out[0], out[1])
+        else:
+            assert ((out[0] - out[1]).double().norm() / out[0].double().norm()).item() < 1e-5
     finally:
         L.nrx_model_destroy(m)
 
