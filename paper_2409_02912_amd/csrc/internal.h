@@ -142,6 +142,7 @@ struct MlpArgs {
                                   // ([s][t][u][b] complex at geo.h_off), outputs j < 2B of the slot
   int n_out;                      // readout: columns of w2 / b2 (0: m_max)
   int only_m;                     // readout (Var-IO): write only the rows of UEs with this many bits (0: all)
+  int fp32_sums;                  // MP, training: the batch has slots of 3 UEs, whose messages are summed in FP32
   int width;                      // channels per row: 128, or 64 (BF16 inference of networks with d <= 64)
 };
 template <typename T>

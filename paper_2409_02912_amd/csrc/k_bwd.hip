@@ -19,6 +19,7 @@
 #include "common.h"
 #include "internal.h"
 #include "conv_common.h"
+#include "mlp_lds.h"
 
 namespace {
 
@@ -613,11 +614,11 @@ __device__ __forceinline__ void gemm_lds(f32x4_t (&acc)[2][8], const unsigned ch
   }
 }
 
-// MP backward for one round.  In: dagg (dL/dagg), m1 (saved hidden), h.
+// MP backward for one round (FP32).  In: dagg (dL/dagg), m1 (saved hidden), h.
 // dmsg_v = sum_{u != v} dagg_u; dm1 = (dmsg W2^T) [m1 > 0]; dh += dm1 W1^T.
 // Writes dmsg and dm1 (for the weight gradients) and updates dh in place.
-template <typename T>
-__global__ __launch_bounds__(256) void mp_bwd_kernel(MpBwdArgs<T> a) {
+__global__ __launch_bounds__(256) void mp_bwd_kernel(MpBwdArgs<float> a) {
+  using T = float;
   constexpr int PB = OpTileB<T>::PITCHB;
   constexpr int MSG_PITCH = NRX_D + 4;
   __shared__ __align__(16) unsigned char lds[128 * MSG_PITCH * 4];
@@ -691,10 +692,6 @@ __global__ __launch_bounds__(256) void mp_bwd_kernel(MpBwdArgs<T> a) {
         if (valid) pack8<T>::load(a.m1 + (gbase + r) * NRX_D + ch0, mv);
 #pragma unroll
         for (int n = 0; n < 8; ++n) v[n] = (valid && mv[n] > 0.f) ? acc[m][n][i] : 0.f;
-        if (sizeof(T) == 2) {
-#pragma unroll
-          for (int n = 0; n < 8; ++n) v[n] = bf2f(f2bf(v[n]));
-        }
         if (valid) pack8<T>::store(a.dm1 + (gbase + r) * NRX_D + ch0, v);
         pack8<T>::store(reinterpret_cast<T *>(lds + r * PB) + ch0, v);
       }
@@ -716,12 +713,12 @@ __global__ __launch_bounds__(256) void mp_bwd_kernel(MpBwdArgs<T> a) {
   }
 }
 
-// Readout backward.  dl (llr layout, masked to j < m_u) -> dr = (dl W2^T) [q > 0],
+// Readout backward (FP32).  dl (llr layout, masked to j < m_u) -> dr = (dl W2^T) [q > 0],
 // dh = dr W1^T.  Per-workgroup partials of dW2 = q^T dl and db2 = sum dl.  One call handles the
 // 8 output columns j0 .. j0 + 7; ReadoutChEst (up to 16 outputs, the gradient in the h layout)
 // takes two calls, the second adding its hidden gradient to dr.
-template <typename T>
-__global__ __launch_bounds__(256) void readout_bwd_kernel(RoBwdArgs<T> a) {
+__global__ __launch_bounds__(256) void readout_bwd_kernel(RoBwdArgs<float> a) {
+  using T = float;
   constexpr int PB = OpTileB<T>::PITCHB;
   __shared__ __align__(16) unsigned char lds[128 * PB];
   __shared__ float red[4][8 * 128 + 8];
@@ -790,10 +787,6 @@ __global__ __launch_bounds__(256) void readout_bwd_kernel(RoBwdArgs<T> a) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) pb[j] += dl[j];
         }
-        if (sizeof(T) == 2) {
-#pragma unroll
-          for (int n = 0; n < 8; ++n) dr[n] = bf2f(f2bf(dr[n]));
-        }
         if (valid) {
           if (a.acc_dr) {
             float o[8], v[8];
@@ -853,6 +846,267 @@ __global__ __launch_bounds__(256) void readout_bwd_kernel(RoBwdArgs<T> a) {
   for (int e = tid; e < 1032; e += 256)
     a.part[(int64_t)blockIdx.x * 1032 + e] = red[0][e] + red[1][e] + red[2][e] + red[3][e];
 }
+
+// BF16 message-passing and readout backward: eight waves that share the weights in LDS and nothing else.  A wave
+// takes 16 rows of a tile from the first load to the last store (its hidden gradient passes through 4 KB of LDS of
+// its own), so the loop has no barrier: the waves drift apart and one's loads run under another's products.  The
+// generic kernels above staged a tile for all waves between seven barriers, one wave per SIMD.  Rows of 4.6 M (64
+// slots x 106 PRB x 4 UEs): message passing 3.67 -> 2.22 ms (7.0 GB), readout 2.50 -> 1.13 ms (3.5 GB); HBM bounds them.
+struct BwdMlp {
+  using Sh = MlpShape<NRX_D>;
+  static constexpr int NW = 8, WAVE_ROWS = 16, HB = WAVE_ROWS * Sh::AROWB;
+  __device__ static __forceinline__ void stage_weights(const bf16_t *w, lds_u8 *lds, int wave, int lane) {
+    const i32x4_t rs = rsrc_words(w, Sh::WB);
+#pragma unroll
+    for (int j = 0; j < Sh::WB / 1024 / NW; ++j) {
+      const int ins = wave + NW * j, row = ins * 16 + (lane >> 2);
+      dma16(rs, lds_addr(lds + ins * 1024), row * 64 + (((lane & 3) ^ swz(row)) << 4));
+    }
+  }
+  // acc = A x W over the 128-deep K; afn(c): the fragment of K chunk c
+  template <typename AF>
+  __device__ static __forceinline__ void gemm(f32x4_t (&acc)[8], const lds_u8 *w, int lr, int lk, AF afn) {
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const v16 af = afn(c);
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) acc[nb] = mfma_bf16(af, ld16(w + Sh::wpos(c, nb, lr, lk)), acc[nb]);
+    }
+  }
+};
+
+__global__ __launch_bounds__(512, 1) void mp_bwd_lds_kernel(MpBwdArgs<bf16_t> a) {
+  using Sh = BwdMlp::Sh;
+  __shared__ __align__(16) unsigned char lds_raw[2 * Sh::WB + BwdMlp::NW * BwdMlp::HB];
+  lds_u8 *lds = (lds_u8 *)lds_raw, *w2t = lds, *w1t = lds + Sh::WB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lk = lane >> 4, ch0 = 8 * lr;
+  lds_u8 *hid = lds + 2 * Sh::WB + wave * BwdMlp::HB;   // this wave's 16 rows
+  BwdMlp::stage_weights(a.w2t, w2t, wave, lane);
+  BwdMlp::stage_weights(a.w1t, w1t, wave, lane);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+    const Tile tl = ldc(a.tiles + tile);
+    const int64_t gbase = ldc(&a.geo[tl.slot].row_base) + tl.row0;
+    const int U = ldc(&a.geo[tl.slot].U);
+    const int rb = wave * 16;
+    if (rb >= tl.nrows) continue;
+    // rows of this lane in the output layout: their m1 and dh, asked for before the products that need them
+    v16 m1[4], dh[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = rb + 4 * lk + i;
+      const int64_t o = (gbase + (r < tl.nrows ? r : 0)) * NRX_D + ch0;
+      m1[i] = ld16(a.m1 + o);
+      dh[i] = ld16(a.dh + o);
+    }
+    // dmsg of row rb + lr, 8 channels per K chunk: the sum over the other UEs of the RE (tiles hold whole REs)
+    const int r = rb + lr, u = r % U;
+    const bool in = r < tl.nrows;
+    f32x4_t acc[8];
+    BwdMlp::gemm(acc, w2t, lr, lk, [&](int c) {
+      float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int o = 0; o < NRX_MAXU; ++o) {
+        if (o < U && o != u && in) {
+          float x[8];
+          pack8<bf16_t>::load(a.dagg + (gbase + r - u + o) * NRX_D + 32 * c + 8 * lk, x);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] += x[k];
+        }
+      }
+      v16 q;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
+      if (in) st16(a.dmsg + (gbase + r) * NRX_D + 32 * c + 8 * lk, q);
+      return q;
+    });
+    // dm1 = acc [m1 > 0]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ri = 4 * lk + i;
+      const bool valid = rb + ri < tl.nrows;
+      float v[8];
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        const float mv = __uint_as_float(n & 1 ? m1[i].w[n / 2] & 0xFFFF0000u : m1[i].w[n / 2] << 16);
+        v[n] = valid && mv > 0.f ? acc[n][i] : 0.f;
+      }
+      v16 q;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(v[2 * k], v[2 * k + 1]);
+      if (valid) st16(a.dm1 + (gbase + rb + ri) * NRX_D + ch0, q);
+      st16(hid + Sh::apos(ri, lr), q);
+    }
+    // (the wave's LDS operations stay in order)
+    BwdMlp::gemm(acc, w1t, lr, lk, [&](int c) { return ld16((const lds_u8 *)hid + Sh::apos(lr, 4 * c + lk)); });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ri = rb + 4 * lk + i;
+      if (ri < tl.nrows) {
+        float v[8];
+#pragma unroll
+        for (int n = 0; n < 8; ++n)
+          v[n] = __uint_as_float(n & 1 ? dh[i].w[n / 2] & 0xFFFF0000u : dh[i].w[n / 2] << 16) + acc[n][i];
+        pack8<bf16_t>::store(a.dh + (gbase + ri) * NRX_D + ch0, v);
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(512, 1) void readout_bwd_lds_kernel(RoBwdArgs<bf16_t> a) {
+  using Sh = BwdMlp::Sh;
+  __shared__ __align__(16) unsigned char lds_raw[Sh::WB + BwdMlp::NW * BwdMlp::HB];
+  __shared__ __align__(16) float w2s[8 * 16][8];   // w2 by (channel of the lane, lane): row 16 n + lr is channel 8 lr + n
+  lds_u8 *lds = (lds_u8 *)lds_raw, *w1t = lds;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lk = lane >> 4, ch0 = 8 * lr;
+  lds_u8 *hid = lds + Sh::WB + wave * BwdMlp::HB;
+  const int M = a.m_max, J0 = a.j0;
+  const int NO = a.n_out ? a.n_out : M;   // columns of w2
+  float pw[8][8], pb[8];                  // this lane's dW2 rows and db2
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    pb[n] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pw[n][j] = 0.f;
+  }
+  for (int e = tid; e < 1024; e += 512) {
+    const int c = e >> 3, j = e & 7;
+    w2s[16 * (c & 7) + (c >> 3)][j] = J0 + j < NO ? a.w2[c * NO + J0 + j] : 0.f;
+  }
+  BwdMlp::stage_weights(a.w1t, w1t, wave, lane);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+    const Tile tl = ldc(a.tiles + tile);
+    const SlotGeo g = a.geo[tl.slot];
+    const int64_t gbase = g.row_base + tl.row0;
+    const int U = g.U, S = g.S, rb = wave * 16;
+    if (rb >= tl.nrows) continue;
+    float dl[4][8], dr[4][8];
+    v16 qv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = rb + 4 * lk + i;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dl[i][j] = 0.f;
+      qv[i] = v16{{0, 0, 0, 0}};
+      if (r < tl.nrows) {
+        const int R = tl.row0 + r;
+        const float *src;
+        int nv;   // columns of the row
+        if (a.chest) {
+          // h layout: row R is entry R of the slot, 2B floats
+          src = a.dllr + (g.h_off + (int64_t)R * g.B) * 2;
+          nv = 2 * g.B;
+        } else {
+          const int s = R / (14 * U), rem = R - s * 14 * U, t = rem / U, u = rem - t * U;
+          const int mu = u == 0 ? g.m[0] : (u == 1 ? g.m[1] : (u == 2 ? g.m[2] : g.m[3]));
+          nv = (!a.only_m || mu == a.only_m) ? (mu < M ? mu : M) : 0;   // Var-IO: not other modulations' rows
+          src = a.dllr + g.llr_off + (((int64_t)u * 14 + t) * S + s) * M;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dl[i][j] = J0 + j < nv ? src[J0 + j] : 0.f;
+        qv[i] = ld16(a.q + (gbase + r) * NRX_D + ch0);
+      }
+      if (lr == 0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pb[j] += dl[i][j];
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const float4 wa = *reinterpret_cast<const float4 *>(w2s[16 * n + lr]);
+      const float4 wb = *reinterpret_cast<const float4 *>(w2s[16 * n + lr] + 4);
+      const float w2[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float q = __uint_as_float(n & 1 ? qv[i].w[n / 2] & 0xFFFF0000u : qv[i].w[n / 2] << 16);
+        float x = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x += dl[i][j] * w2[j];
+        dr[i][n] = q > 0.f ? x : 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pw[n][j] += q * dl[i][j];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ri = 4 * lk + i, r = rb + ri;
+      v16 q;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q.w[k] = pack_bf2(dr[i][2 * k], dr[i][2 * k + 1]);
+      if (r < tl.nrows) {
+        bf16_t *d = a.dr + (gbase + r) * NRX_D + ch0;
+        if (a.acc_dr) {
+          float o[8], v[8];
+          pack8<bf16_t>::load(d, o);
+#pragma unroll
+          for (int n = 0; n < 8; ++n) v[n] = o[n] + bf2f(f2bf(dr[i][n]));
+          pack8<bf16_t>::store(d, v);
+        } else {
+          st16(d, q);
+        }
+      }
+      st16(hid + Sh::apos(ri, lr), q);
+    }
+    f32x4_t acc[8];
+    BwdMlp::gemm(acc, w1t, lr, lk, [&](int c) { return ld16((const lds_u8 *)hid + Sh::apos(lr, 4 * c + lk)); });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = rb + 4 * lk + i;
+      if (r < tl.nrows) {
+        bf16_t *d = a.dh + (gbase + r) * NRX_D + ch0;
+        float v[8];
+#pragma unroll
+        for (int n = 0; n < 8; ++n) v[n] = acc[n][i];
+        if (a.accumulate) {
+          float o[8];
+          pack8<bf16_t>::load(d, o);
+#pragma unroll
+          for (int n = 0; n < 8; ++n) v[n] += o[n];
+        }
+        pack8<bf16_t>::store(d, v);
+      }
+    }
+  }
+  // reduce dW2 / db2 over the 4 row groups of a wave, then over the waves, through the weights' LDS
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      pw[n][j] += __shfl_xor(pw[n][j], 16, 64);
+      pw[n][j] += __shfl_xor(pw[n][j], 32, 64);
+    }
+    pb[n] += __shfl_xor(pb[n], 16, 64);
+    pb[n] += __shfl_xor(pb[n], 32, 64);
+  }
+  __syncthreads();
+  float *red = reinterpret_cast<float *>(lds_raw);   // [8 waves][1032]
+  if (lk == 0) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) red[wave * 1032 + (ch0 + n) * 8 + j] = pw[n][j];
+    if (lr == 0)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) red[wave * 1032 + 1024 + j] = pb[j];
+  }
+  __syncthreads();
+  for (int e = tid; e < 1032; e += 512) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < BwdMlp::NW; ++w) v += red[w * 1032 + e];
+    a.part[(int64_t)blockIdx.x * 1032 + e] = v;
+  }
+}
+static_assert(BwdMlp::NW * 1032 * 4 <= BwdMlp::Sh::WB + BwdMlp::NW * BwdMlp::HB, "reduction space");
 
 // One thread per 8 channels (16 or 32 bytes) of a row; grid (row blocks, slots).
 template <typename T>
@@ -924,7 +1178,8 @@ void launch_ln_reduce(const float *part, int n, int64_t g_off, int64_t b_off, fl
 }
 template <typename T>
 void launch_mp_bwd(const MpBwdArgs<T> &a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(mp_bwd_kernel<T>, dim3(grid), dim3(256), 0, st, a);
+  if constexpr (std::is_same<T, bf16_t>::value) hipLaunchKernelGGL(mp_bwd_lds_kernel, dim3(grid), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL(mp_bwd_kernel, dim3(grid), dim3(256), 0, st, a);
 }
 template <typename T>
 void launch_select_rows(const T *src, const SlotGeo *geo, int n_slots, int64_t max_rows, int only_m, T *dst,
@@ -937,7 +1192,9 @@ template void launch_select_rows<bf16_t>(const bf16_t *, const SlotGeo *, int, i
 
 template <typename T>
 void launch_readout_bwd(const RoBwdArgs<T> &a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(readout_bwd_kernel<T>, dim3(grid), dim3(256), 0, st, a);
+  if constexpr (std::is_same<T, bf16_t>::value)
+    hipLaunchKernelGGL(readout_bwd_lds_kernel, dim3(grid), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL(readout_bwd_kernel, dim3(grid), dim3(256), 0, st, a);
 }
 void launch_readout_w2_reduce(const float *part, int n, int m_max, int64_t w2_off, int64_t b2_off, float *dw,
                               hipStream_t st, int j0) {

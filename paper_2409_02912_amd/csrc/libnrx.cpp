@@ -1211,6 +1211,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
       ma.tiles = D.mt;
       ma.n_tiles = (int)P->mt.size();
       ma.width = m->width;
+      for (auto &g : P->geo) ma.fp32_sums |= g.U == 3;
       if (persist) {
         add_stage(PK_MP, &ma);
       } else {
@@ -1710,7 +1711,9 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
   float *lpart = (float *)(ws + L.lpart), *rpart = (float *)(ws + L.rpart);
   const int d = NRX_D;
   const int ti256 = tile_size_index(4);
-  const int grid_mlp = std::min<int>((int)std::max(P->mt.size(), P->rt.size()), std::min(num_cu() * 4, BWD_GRID_MAX));
+  // one workgroup of eight waves per CU in BF16, the generic kernels several of four
+  const int grid_mlp = std::min<int>((int)std::max(P->mt.size(), P->rt.size()),
+                                     std::min(num_cu() * (std::is_same<T, bf16_t>::value ? 1 : 4), BWD_GRID_MAX));
 
   // weight gradient of a layer, and its bias gradient: from the same pass over dY in BF16; in FP32, and where the
   // layer folds positional-encoding channels into a table (pe_w_off), from column sums per table entry

@@ -77,8 +77,9 @@ struct SubTiles {
   __device__ int next(int i) const { return i + 1; }
 };
 
-// lds: MlpShape<W>::MP_LDS bytes (both weight matrices, then two tile buffers).
-template <int NW, int W = NRX_D, typename Src>
+// lds: MlpShape<W>::MP_LDS bytes (both weight matrices, then two tile buffers).  SAVE: the hidden activations are
+// kept for the backward pass (a.save_m1).
+template <int NW, int W = NRX_D, bool SAVE = false, typename Src>
 __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src &src, lds_u8 *lds) {
   using Sh = MlpShape<W>;
   constexpr int NB = Sh::NB, CH = Sh::CH, PIECES = Sh::PIECES, AROWB = Sh::AROWB, TILEB = Sh::TILEB, WB = Sh::WB;
@@ -166,6 +167,8 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
           v[nb] = x > 0.f ? x : 0.f;
         }
         Sh::put(t, r, lr, v);
+        if constexpr (SAVE)
+          if (r < tl.nrows) packn<bf16_t, NB>::store(a.save_m1 + (g.row_base + tl.row0 + r) * W + ch0, v);
       }
     gemm(lw2);
     auto emit = [&](int r, const float *v) {
@@ -241,7 +244,7 @@ __device__ __forceinline__ void mp_lds_body(const MlpArgs<bf16_t> &a, const Src 
 // copied to LDS once, 128-row tiles are DMA'd one ahead, and the hidden layer is
 // written back over the wave's own rows.
 // lds: MlpShape<W>::RO_LDS bytes (first- and second-layer weights, then two tile buffers).
-template <int NW, int W = NRX_D, typename Src>
+template <int NW, int W = NRX_D, bool SAVE = false, typename Src>
 __device__ __forceinline__ void readout_lds_body(const MlpArgs<bf16_t> &a, const Src &src, lds_u8 *lds) {
   using Sh = MlpShape<W>;
   constexpr int NB = Sh::NB, CH = Sh::CH, AROWB = Sh::AROWB, TILEB = Sh::TILEB, WB = Sh::WB, W2B = Sh::W2B;
@@ -327,6 +330,17 @@ __device__ __forceinline__ void readout_lds_body(const MlpArgs<bf16_t> &a, const
           v[nb] = x > 0.f ? x : 0.f;
         }
         Sh::put(t, rbase + mb * 16 + 4 * lk + i, lr, v);
+        if constexpr (SAVE) {   // training (Var-IO: every readout keeps its own modulation's rows only)
+          const int r = rbase + mb * 16 + 4 * lk + i;
+          bool keep = r < tl.nrows;
+          if (a.only_m) {
+            const int u = (tl.row0 + r) % U;
+            const int mu = u == 0 ? ldc(&a.geo[tl.slot].m[0]) : (u == 1 ? ldc(&a.geo[tl.slot].m[1])
+                         : (u == 2 ? ldc(&a.geo[tl.slot].m[2]) : ldc(&a.geo[tl.slot].m[3])));
+            keep = keep && mu == a.only_m;
+          }
+          if (keep) packn<bf16_t, NB>::store(a.save_m1 + (g.row_base + tl.row0 + r) * W + ch0, v);
+        }
       }
     // second layer: one 16-column block
     f32x4_t o[MBW];
