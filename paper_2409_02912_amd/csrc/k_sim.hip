@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void sim_taps_kernel(SimParams p, const SlotGe
   g[tap_off[slot] + e] = make_float2(0.25f * re, 0.25f * im);
 }
 
-// spatial mixing and PDP weight: hm[((u*B + b)*14 + t)*L + l], the taps of an antenna and symbol together
+// spatial mixing and PDP weight: hm[((u*14 + t)*B + b)*L + l], the taps of an antenna and symbol together
 __global__ void sim_mix_kernel(SimParams p, const SlotGeo *geo, const int64_t *tap_off, const float2 *g, float2 *hm) {
   const int slot = blockIdx.y;
   const SlotGeo G = geo[slot];
@@ -112,124 +112,127 @@ __global__ void sim_mix_kernel(SimParams p, const SlotGeo *geo, const int64_t *t
     const float2 v = gs[((int64_t)((u * B + bp) * L + l)) * 14 + t];
     re += c * v.x; im += c * v.y;
   }
-  hm[tap_off[slot] + ((int64_t)(u * B + b) * 14 + t) * L + l] = make_float2(amp * re, amp * im);
+  hm[tap_off[slot] + ((int64_t)(u * 14 + t) * B + b) * L + l] = make_float2(amp * re, amp * im);
 }
 
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(8)));   // two complex samples at any sample offset
 
-// The grid: a workgroup takes 64 consecutive subcarriers of a slot, its four waves every fourth symbol, a lane one
-// subcarrier.  The taps of an (UE, antenna, symbol) are then the same for a whole wave: they come by scalar loads
-// and enter the sums as scalar operands, and each lane keeps its subcarrier's LT phases in registers for all of
-// its symbols.  With one thread per RE and a run-time tap count the phases were an array in memory and every lane
-// read its own taps: 1.70 ms for 64 slots x 106 PRB, 8 antennas, 4 UEs, 12 taps, now 0.38 ms (the Philox and Box-Muller
-// arithmetic of the noise is about half of that).  Samples and
-// channels go out two antennas (16 bytes) at a time.  The data bits are drawn here anyway and are written here.
+// The grid.  The channel of a subcarrier is the product of the taps [antenna and symbol][tap] and the subcarrier's phases
+// [tap][subcarrier], complex: as real matrices, rows (antenna and symbol, re / im), columns subcarriers, summed over (tap,
+// cos / sin), it is FP32 matrix-core work (16x16x4), and the vector units are left to the random numbers.  A workgroup
+// takes 64 consecutive subcarriers of a slot.  Its threads first draw the data symbols of all UEs into LDS (and write the
+// bits); then each wave takes 16 of the subcarriers through all symbols.  j = 14-symbol x antenna index t B + b: a wave's
+// product covers 8 of them, and a lane's part of the result is two consecutive j of one subcarrier, which go out as 16
+// bytes (64 consecutive per subcarrier and instruction).  A lane is the column of the phases that it computes itself (taps
+// 3 - q + 4 i, q = lane / 16).  64 slots x 106 PRB, 8 antennas, 4 UEs, 12 taps: 0.148 ms
+// (2.5 TB/s of its writes; the random numbers and their conversions are what is left), 0.383 ms with the taps as scalar
+// operands of vector products and 16 bytes per subcarrier and store, 1.70 ms with the phases in memory.
 // EXACT: n_taps = LT; else n_taps <= LT.
 template <int LT, bool EXACT>
 __global__ __launch_bounds__(256) void sim_grid_kernel(SimParams p, const SlotGeo *geo, const int64_t *tap_off,
                                                        const float2 *hm, const float2 *dmrs, const float *n0_ws,
                                                        int m_max, float2 *y, float2 *h_true, uint8_t *bits) {
-  typedef const __attribute__((address_space(4))) float cfloat;
+  constexpr int NI = (LT + 3) / 4;
+  __shared__ float2 xs[NRX_MAXU * 14 * 64];   // transmitted symbols [u][t][subcarrier]
   const int slot = blockIdx.y;
   const SlotGeo G = geo[slot];
   const int S = G.S, U = G.U, B = G.B, L = EXACT ? LT : p.n_taps;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (blockIdx.x * 64 >= S) return;
-  const int s = blockIdx.x * 64 + (threadIdx.x & 63);
+  for (int k = wave; k < 14 * U; k += 4) {   // a (UE, symbol) per wave
+    const int u = k / 14, t = k - u * 14, s = blockIdx.x * 64 + lane;
+    float2 x = make_float2(0.f, 0.f);
+    if (s < S) {
+      if (t == NRX_DMRS0 || t == NRX_DMRS1) {
+        const int delta = u >> 1;
+        if (((s - delta) & 1) == 0) {
+          const int n = (s - delta) >> 2, kp = ((s - delta) >> 1) & 1;
+          const float2 r = dmrs[G.dmrs_off + (t == NRX_DMRS1 ? S / 2 : 0) + 2 * n + kp];
+          const float w = ((u & 1) && kp) ? -1.f : 1.f;
+          x = make_float2(w * r.x, w * r.y);
+        }
+      } else {
+        const int tdata = t < NRX_DMRS0 ? t : (t < NRX_DMRS1 ? t - 1 : t - 2);
+        const uint32_t e = (uint32_t)(tdata * S + s);
+        const int m = geo[slot].m[u];
+        const uint32_t w0 = draw(p, slot, 1, ((uint32_t)u << 16) | e).x & ((1u << m) - 1u);
+        x = qam(w0, m);
+        if (bits) {
+          uint8_t *dst = bits + G.bits_off + ((int64_t)u * S * 12 + e) * m_max;
+          for (int j = 0; j < m_max; ++j) dst[j] = (uint8_t)((w0 >> j) & 1u);
+        }
+      }
+    }
+    xs[k * 64 + lane] = x;
+  }
+  __syncthreads();
+  const int q = lane >> 4, sl = wave * 16 + (lane & 15), s = blockIdx.x * 64 + sl;
+  if (blockIdx.x * 64 + wave * 16 >= S) return;
   const bool in = s < S;
-  float2 ph[LT];
+  float pc[NI], ps[NI];   // phases of the taps q + 4 i: columns of the second operand
 #pragma unroll
-  for (int l = 0; l < LT; ++l) {
-    ph[l] = make_float2(0.f, 0.f);
-    if (EXACT || l < L) {
+  for (int i = 0; i < NI; ++i) {
+    const int l = 3 - q + 4 * i;
+    pc[i] = ps[i] = 0.f;
+    if (l < L) {
       const int64_t idx = ((int64_t)s * l * p.scs_khz * p.tap_spacing_ns) % 1000000;
-      float sn, cs;
-      sincosf(-6.28318530717958648f * ((float)idx * 1e-6f), &sn, &cs);
-      ph[l] = make_float2(cs, sn);
+      sincosf(-6.28318530717958648f * ((float)idx * 1e-6f), &ps[i], &pc[i]);
     }
   }
   const float sig = sqrtf(n0_ws[slot] * 0.5f);
-  const int64_t toff = tap_off[slot];
+  const int J = 14 * B;
+  const float2 *hs = hm + tap_off[slot];
+  auto noise = [&](int j) {
+    const u4 w = draw(p, slot, 3, (uint32_t)(s * J + j));
+    const float r = sig * sqrtf(-2.f * logf(unif(w.x)));
+    float sn, cs;
+    sincospif(2.f * unif(w.y), &sn, &cs);   // (the argument is exact)
+    return make_float2(r * cs, r * sn);
+  };
 #pragma unroll 1
-  for (int t = wave; t < 14; t += 4) {
-    const bool is_dmrs = (t == NRX_DMRS0 || t == NRX_DMRS1);
-    const int tdata = t < NRX_DMRS0 ? t : (t < NRX_DMRS1 ? t - 1 : t - 2);
-    float2 x[NRX_MAXU];
+  for (int j0 = 0; j0 < J; j0 += 8) {
+    const int jr = j0 + ((lane & 15) >> 1);         // this lane's row of the taps: j, and re (even lanes) or im
+    f32x4_t hv[NRX_MAXU];
 #pragma unroll
     for (int u = 0; u < NRX_MAXU; ++u) {
-      x[u] = make_float2(0.f, 0.f);
-      if (u < U && in) {
-        if (is_dmrs) {
-          const int delta = u >> 1;
-          if (((s - delta) & 1) == 0) {
-            const int n = (s - delta) >> 2, kp = ((s - delta) >> 1) & 1;
-            const float2 r = dmrs[G.dmrs_off + (t == NRX_DMRS1 ? S / 2 : 0) + 2 * n + kp];
-            const float w = ((u & 1) && kp) ? -1.f : 1.f;
-            x[u] = make_float2(w * r.x, w * r.y);
-          }
-        } else {
-          const uint32_t e = (uint32_t)(tdata * S + s);
-          const uint32_t w0 = draw(p, slot, 1, ((uint32_t)u << 16) | e).x & ((1u << G.m[u]) - 1u);
-          x[u] = qam(w0, G.m[u]);
-          if (bits) {
-            uint8_t *dst = bits + G.bits_off + ((int64_t)u * S * 12 + e) * m_max;
-            for (int j = 0; j < m_max; ++j) dst[j] = (uint8_t)((w0 >> j) & 1u);
+      hv[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (u < U) {
+        const float2 *hp = hs + ((int64_t)u * J + jr) * L + 3 - q;
+        f32x4_t hc = hv[u];   // (the cosines' sum and the sines' apart, the weak late taps first: least rounding)
+#pragma unroll
+        for (int i = NI - 1; i >= 0; --i) {
+          const float2 a = jr < J && 3 - q + 4 * i < L ? hp[4 * i] : make_float2(0.f, 0.f);
+          hc = __builtin_amdgcn_mfma_f32_16x16x4f32(lane & 1 ? a.y : a.x, pc[i], hc, 0, 0, 0);
+          hv[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(lane & 1 ? a.x : -a.y, ps[i], hv[u], 0, 0, 0);
+        }
+        hv[u] += hc;
+      }
+    }
+    const int j = j0 + 2 * q;                       // this lane's part of the result: j and j + 1
+    if (j >= J || !in) continue;                    // (J is even; no barrier follows)
+    const int t0 = j / B, t1 = (j + 1) / B, b0 = j - t0 * B, b1 = j + 1 - t1 * B;
+    float2 y0 = make_float2(0.f, 0.f), y1 = y0;
+#pragma unroll
+    for (int u = 0; u < NRX_MAXU; ++u) {
+      if (u < U) {
+        const float2 x0 = xs[(u * 14 + t0) * 64 + sl], x1 = xs[(u * 14 + t1) * 64 + sl];
+        const f32x4_t h = hv[u];
+        y0 = make_float2(fmaf(-h[1], x0.y, fmaf(h[0], x0.x, y0.x)), fmaf(h[1], x0.x, fmaf(h[0], x0.y, y0.y)));
+        y1 = make_float2(fmaf(-h[3], x1.y, fmaf(h[2], x1.x, y1.x)), fmaf(h[3], x1.x, fmaf(h[2], x1.y, y1.y)));
+        if (h_true) {
+          float2 *d = h_true + G.h_off + (int64_t)s * J * U;
+          if (t0 == t1) {
+            *reinterpret_cast<f32x4u *>(d + (t0 * U + u) * B + b0) = f32x4u{h[0], h[1], h[2], h[3]};
+          } else {
+            d[(t0 * U + u) * B + b0] = make_float2(h[0], h[1]);
+            d[(t1 * U + u) * B + b1] = make_float2(h[2], h[3]);
           }
         }
       }
     }
-    // channel of UE u at antenna b: taps by scalar loads
-    auto channel = [&](int u, int b) {
-      cfloat *hp = (cfloat *)(hm + toff + ((int64_t)(u * B + b) * 14 + t) * L);
-      float hr = 0.f, hi = 0.f;
-#pragma unroll
-      for (int l = 0; l < LT; ++l) {
-        if (EXACT || l < L) {
-          const float ax = hp[2 * l], ay = hp[2 * l + 1];
-          hr += ax * ph[l].x - ay * ph[l].y;
-          hi += ax * ph[l].y + ay * ph[l].x;
-        }
-      }
-      return make_float2(hr, hi);
-    };
-    auto noise = [&](int b) {
-      const u4 w = draw(p, slot, 3, (uint32_t)((s * 14 + t) * B + b));
-      const float r = sqrtf(-2.f * logf(unif(w.x)));
-      float sn, cs;
-      sincosf(6.28318530717958648f * unif(w.y), &sn, &cs);
-      return make_float2(sig * r * cs, sig * r * sn);
-    };
-    const int64_t yo = G.y_off + ((int64_t)s * 14 + t) * B, ho = G.h_off + ((int64_t)s * 14 + t) * U * B;
-#pragma unroll 1
-    for (int b = 0; b < B; b += 2) {
-      const bool two = b + 1 < B;
-      float2 y0 = make_float2(0.f, 0.f), y1 = y0;
-#pragma unroll
-      for (int u = 0; u < NRX_MAXU; ++u) {
-        if (u < U) {
-          const float2 h0 = channel(u, b), h1 = channel(u, two ? b + 1 : b);
-          y0.x += h0.x * x[u].x - h0.y * x[u].y;
-          y0.y += h0.x * x[u].y + h0.y * x[u].x;
-          y1.x += h1.x * x[u].x - h1.y * x[u].y;
-          y1.y += h1.x * x[u].y + h1.y * x[u].x;
-          if (h_true && in) {
-            float2 *d = h_true + ho + u * B + b;
-            if (two) *reinterpret_cast<f32x4u *>(d) = f32x4u{h0.x, h0.y, h1.x, h1.y};
-            else *d = h0;
-          }
-        }
-      }
-      if (in) {
-        const float2 n0 = noise(b);
-        y0 = make_float2(y0.x + n0.x, y0.y + n0.y);
-        if (two) {
-          const float2 n1 = noise(b + 1);
-          *reinterpret_cast<f32x4u *>(y + yo + b) = f32x4u{y0.x, y0.y, y1.x + n1.x, y1.y + n1.y};
-        } else {
-          y[yo + b] = y0;
-        }
-      }
-    }
+    const float2 n0 = noise(j), n1 = noise(j + 1);
+    *reinterpret_cast<f32x4u *>(y + G.y_off + (int64_t)s * J + j) =
+        f32x4u{y0.x + n0.x, y0.y + n0.y, y1.x + n1.x, y1.y + n1.y};
   }
 }
 
