@@ -15,10 +15,11 @@
 // few LS pairs around them.  The UE count and the bits per axis are template parameters: with run-time bounds
 // the matrices are indexed arrays in scratch memory, which is what bounded the kernel (64 slots x 106 PRB, 16
 // antennas, 4 UEs, 64-QAM: 4.3 ms, and 0.7 ms more for an estimate written to memory and read back).  Without
-// a given estimate the threads interpolate the LS pairs themselves: two symbols x two pairs per (UE, antenna)
-// from the cache instead of 8 U B bytes per RE from memory.  That batch now takes 0.25 ms for the whole call
-// (5.16 ms before), 1.0 TB/s of its samples and LLRs; the fp64 products of the Gram matrix and the pair loads
-// bound it.
+// a given estimate a workgroup interpolates the LS pairs itself: in frequency once, into LDS, for its 12 symbols to share,
+// in time per thread.  A thread reads its samples eight antennas at once: other lanes' samples are on other lines, and
+// antenna by antenna the lines left the L1 cache between their reads.  That batch's kernel takes 0.11 ms, 2.0 TB/s of
+// its samples and LLRs (0.22 ms with four pair loads and three interpolations per thread, UE and antenna); the fp64
+// products of the Gram matrix, the solves and the demapper's minima, about 11,000 cycles a wave, bound it.
 #include "common.h"
 #include "internal.h"
 #include "ls_interp.h"
@@ -88,20 +89,21 @@ __device__ __forceinline__ void store_llr(float zr, float zi, float inv_var, flo
 
 constexpr int LM_SC = 16;                  // subcarriers of a workgroup
 constexpr int LM_THREADS = 12 * LM_SC;     // x data symbols
+constexpr int LM_ANT = 16;                 // antennas, at most
+constexpr int LM_ROW = NRX_MAXU * LM_ANT + 2;   // estimates of a (DMRS symbol, subcarrier) [u][b]; rows 4 banks apart mod 64
 
-// One data RE (s, t) of a slot with U UEs.  LS: the estimate is interpolated from the slot's pairs.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(8)));   // two complex samples at any sample offset
+
+// One data RE (s, t) of a slot with U UEs.  LS: the estimate of the two DMRS symbols at this subcarrier is in LDS rows
+// hl and hl + LM_SC LM_ROW, between which the symbol is interpolated.
 template <int U, bool LS>
 __device__ __forceinline__ void lmmse_re(const SlotGeo &g, int s, int t, int m_max, const float2 *y, const float2 *h,
-                                         const float2 *P, double n0, bool erase, float *llr) {
+                                         const float2 *hl, double n0, bool erase, float *llr) {
   constexpr int NO = U * (U - 1) / 2 > 0 ? U * (U - 1) / 2 : 1;
-  const int S = g.S, B = g.B, np = S / 4;
+  const int S = g.S, B = g.B;
   const float2 *yr = y + g.y_off + ((int64_t)s * 14 + t) * B;
   const float2 *hr = LS ? nullptr : h + g.h_off + ((int64_t)s * 14 + t) * U * B;
-  LsPoint q[2];   // CDM groups 0 and 1
-  if constexpr (LS) {
-    q[0] = ls_point(s, t, 0, np);
-    q[1] = ls_point(s, t, 1, np);
-  }
+  const LsPoint q = ls_point(s, t, 0, S / 4);   // (the weights of the DMRS symbols depend on t alone)
   double gd[U];        // diagonal of G = H^H H (+ N0)
   cd go[NO], rhs[U];   // G[u][v] = sum_b conj(h_u) h_v, u > v, at u (u - 1) / 2 + v
 #pragma unroll
@@ -111,15 +113,10 @@ __device__ __forceinline__ void lmmse_re(const SlotGeo &g, int s, int t, int m_m
 #pragma unroll
     for (int v = 0; v < u; ++v) go[u * (u - 1) / 2 + v] = {0, 0};
   }
-#pragma unroll 2
-  for (int b = 0; b < B; ++b) {
+  auto antenna = [&](const float2 (&x)[U], float2 yq) {
     cd hb[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float2 x = LS ? ls_interp(P, q[u >> 1], U, u, B, b, np) : hr[u * B + b];
-      hb[u] = {(double)x.x, (double)x.y};
-    }
-    const float2 yq = yr[b];
+    for (int u = 0; u < U; ++u) hb[u] = {(double)x[u].x, (double)x[u].y};
     const cd yb = {(double)yq.x, (double)yq.y};
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -132,6 +129,46 @@ __device__ __forceinline__ void lmmse_re(const SlotGeo &g, int s, int t, int m_m
         o.re += hb[u].re * hb[v].re + hb[u].im * hb[v].im;
         o.im += hb[u].re * hb[v].im - hb[u].im * hb[v].re;
       }
+    }
+  };
+  if constexpr (LS) {
+    // antennas in pairs, the samples of eight at a time: their 64 bytes are a line that no other lane reads
+    auto two = [&](int b, f32x4u yv) {
+      float2 x0[U], x1[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float4 h0 = *reinterpret_cast<const float4 *>(hl + u * LM_ANT + b);
+        const float4 h1 = *reinterpret_cast<const float4 *>(hl + LM_SC * LM_ROW + u * LM_ANT + b);
+        x0[u] = ls_mix_time(q, make_float2(h0.x, h0.y), make_float2(h1.x, h1.y));
+        x1[u] = ls_mix_time(q, make_float2(h0.z, h0.w), make_float2(h1.z, h1.w));
+      }
+      antenna(x0, make_float2(yv[0], yv[1]));
+      antenna(x1, make_float2(yv[2], yv[3]));
+    };
+    int b = 0;
+#pragma unroll 1
+    for (; b + 8 <= B; b += 8) {
+      f32x4u yv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) yv[k] = *reinterpret_cast<const f32x4u *>(yr + b + 2 * k);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) two(b + 2 * k, yv[k]);
+    }
+#pragma unroll 1
+    for (; b + 2 <= B; b += 2) two(b, *reinterpret_cast<const f32x4u *>(yr + b));
+    if (b < B) {
+      float2 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = ls_mix_time(q, hl[u * LM_ANT + b], hl[LM_SC * LM_ROW + u * LM_ANT + b]);
+      antenna(x, yr[b]);
+    }
+  } else {
+#pragma unroll 2
+    for (int b = 0; b < B; ++b) {
+      float2 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = hr[u * B + b];
+      antenna(x, yr[b]);
     }
   }
 #pragma unroll
@@ -208,6 +245,21 @@ __global__ __launch_bounds__(LM_THREADS) void lmmse_kernel(const SlotGeo *geo, i
   const SlotGeo g = geo[slot];
   const int S = g.S, U = g.U, s0 = blockIdx.x * LM_SC;
   if (s0 >= S) return;
+  __shared__ __align__(16) float2 hl[LS ? 2 * LM_SC * LM_ROW : 1];
+  if constexpr (LS) {
+    // the pairs interpolated to the workgroup's subcarriers at the two DMRS symbols, for its 12 data symbols to share
+    const float2 *P = pairs + pair_off[slot];
+    const int B = g.B, np = S / 4;
+    const int bb = 32 - __clz(B - 1), ub = 32 - __clz(U - 1);   // bits of an antenna's and a UE's index
+    for (int e = threadIdx.x; e < 2 * LM_SC << (bb + ub); e += LM_THREADS) {
+      const int b = e & ((1 << bb) - 1), u = (e >> bb) & ((1 << ub) - 1), k = e >> (bb + ub), li = k / LM_SC, sl = k % LM_SC;
+      if (b >= B || u >= U) continue;
+      const LsPoint q = ls_point(min(s0 + sl, S - 1), 0, u >> 1, np);
+      const float2 *r = P + ((int64_t)li * U + u) * np * B + b;
+      hl[k * LM_ROW + u * LM_ANT + b] = ls_mix_freq(q, r[q.n0 * B], r[q.n1 * B]);
+    }
+    __syncthreads();
+  }
   // the DMRS symbols carry no data: zeros
   for (int e = threadIdx.x; e < 2 * U * LM_SC; e += LM_THREADS) {
     const int s = s0 + e % LM_SC, t = (e / LM_SC) & 1 ? NRX_DMRS1 : NRX_DMRS0, u = e / (2 * LM_SC);
@@ -218,13 +270,13 @@ __global__ __launch_bounds__(LM_THREADS) void lmmse_kernel(const SlotGeo *geo, i
   if (s >= S) return;
   const int t = td < NRX_DMRS0 ? td : (td < NRX_DMRS1 - 1 ? td + 1 : td + 2);
   const double n0 = n0dev ? (double)n0dev[slot] : (double)g.n0;
-  const float2 *P = LS ? pairs + pair_off[slot] : nullptr;
+  const float2 *row = hl + (LS ? (threadIdx.x % LM_SC) * LM_ROW : 0);
   const bool erase = slot_mask != nullptr;
   switch (U) {   // uniform
-    case 1: lmmse_re<1, LS>(g, s, t, m_max, y, h, P, n0, erase, llr); break;
-    case 2: lmmse_re<2, LS>(g, s, t, m_max, y, h, P, n0, erase, llr); break;
-    case 3: lmmse_re<3, LS>(g, s, t, m_max, y, h, P, n0, erase, llr); break;
-    default: lmmse_re<4, LS>(g, s, t, m_max, y, h, P, n0, erase, llr); break;
+    case 1: lmmse_re<1, LS>(g, s, t, m_max, y, h, row, n0, erase, llr); break;
+    case 2: lmmse_re<2, LS>(g, s, t, m_max, y, h, row, n0, erase, llr); break;
+    case 3: lmmse_re<3, LS>(g, s, t, m_max, y, h, row, n0, erase, llr); break;
+    default: lmmse_re<4, LS>(g, s, t, m_max, y, h, row, n0, erase, llr); break;
   }
 }
 

@@ -25,23 +25,22 @@ __device__ __forceinline__ LsPoint ls_point(int s, int t, int delta, int np) {
 }
 
 // (fused products spelled out: every user of the estimate gets the same bits)
-__device__ __forceinline__ float2 ls_mix(const LsPoint &q, const float2 (&a0)[2], const float2 (&a1)[2]) {
-  float2 hl[2];
-#pragma unroll
-  for (int li = 0; li < 2; ++li)
-    hl[li] = make_float2(fmaf(1.f - q.w, a0[li].x, q.w * a1[li].x), fmaf(1.f - q.w, a0[li].y, q.w * a1[li].y));
-  return make_float2(fmaf(q.wt0, hl[0].x, q.wt1 * hl[1].x), fmaf(q.wt0, hl[0].y, q.wt1 * hl[1].y));
+__device__ __forceinline__ float2 ls_mix_freq(const LsPoint &q, float2 a0, float2 a1) {
+  return make_float2(fmaf(1.f - q.w, a0.x, q.w * a1.x), fmaf(1.f - q.w, a0.y, q.w * a1.y));
+}
+__device__ __forceinline__ float2 ls_mix_time(const LsPoint &q, float2 h0, float2 h1) {
+  return make_float2(fmaf(q.wt0, h0.x, q.wt1 * h1.x), fmaf(q.wt0, h0.y, q.wt1 * h1.y));
 }
 
 // estimate of UE u at antenna b from the slot's pairs P
 __device__ __forceinline__ float2 ls_interp(const float2 *P, const LsPoint &q, int U, int u, int B, int b, int np) {
-  float2 a0[2], a1[2];
+  float2 hl[2];
 #pragma unroll
   for (int li = 0; li < 2; ++li) {
-    a0[li] = P[(((int64_t)li * U + u) * np + q.n0) * B + b];
-    a1[li] = P[(((int64_t)li * U + u) * np + q.n1) * B + b];
+    const float2 *r = P + ((int64_t)li * U + u) * np * B + b;
+    hl[li] = ls_mix_freq(q, r[(int64_t)q.n0 * B], r[(int64_t)q.n1 * B]);
   }
-  return ls_mix(q, a0, a1);
+  return ls_mix_time(q, hl[0], hl[1]);
 }
 
 }  // namespace
