@@ -136,6 +136,7 @@ struct Plan {
   // device table blob
   size_t off_geo = 0, off_ct[N_TILE_SIZES] = {}, off_mt = 0, off_rt = 0, off_pair = 0, off_tap = 0;
   size_t off_ptb = 0, off_pib = 0, off_ptr = 0, off_pg = 0, meta_bytes = 0;
+  size_t slot_bytes = 0;   // the first part of the tables: what is indexed by slot alone
   size_t off_ctm[NRX_N_MODS][N_TILE_SIZES] = {}, off_rtm[NRX_N_MODS] = {};
   std::vector<char> blob;        // host image of the device tables
   void *pinned = nullptr;        // pinned copy, allocated on first upload
@@ -339,11 +340,12 @@ nrx_status get_plan(const nrx_slot_desc *d, int n, int max_ant, int m_max, int s
   }
   size_t o = 0;
   P->off_geo = o; o = align256(o + sizeof(SlotGeo) * P->geo.size());
+  P->off_pair = o; o = align256(o + sizeof(int64_t) * P->pair_off.size());
+  P->off_tap = o; o = align256(o + sizeof(int64_t) * P->tap_off.size());
+  P->slot_bytes = o;
   for (int k = 0; k < N_TILE_SIZES; ++k) { P->off_ct[k] = o; o = align256(o + sizeof(Tile) * P->ct[k].size()); }
   P->off_mt = o; o = align256(o + sizeof(Tile) * P->mt.size());
   P->off_rt = o; o = align256(o + sizeof(Tile) * P->rt.size());
-  P->off_pair = o; o = align256(o + sizeof(int64_t) * P->pair_off.size());
-  P->off_tap = o; o = align256(o + sizeof(int64_t) * P->tap_off.size());
   P->off_ptb = o; o = align256(o + sizeof(int32_t) * P->ptile_base.size());
   P->off_pib = o; o = align256(o + sizeof(int32_t) * P->pitem_base.size());
   P->off_ptr = o; o = align256(o + sizeof(int32_t) * P->ptile_rows.size());
@@ -375,8 +377,10 @@ nrx_status get_plan(const nrx_slot_desc *d, int n, int max_ant, int m_max, int s
   return NRX_OK;
 }
 
-// Enqueues the copy of the plan's device tables into the workspace.
-nrx_status plan_upload(Plan *P, char *dst, hipStream_t st) {
+// Enqueues the copy of the plan's device tables into the workspace.  slots_only: without the lists of row tiles, which
+// only the network's kernels read (64 slots x 106 PRB, 4 UEs:
+// 2.9 MB, 60 us before the first kernel could start; one slot of 273 PRB, 2 UEs: 47 KB, 13 us).
+nrx_status plan_upload(Plan *P, char *dst, hipStream_t st, bool slots_only = false) {
   {
     std::lock_guard<std::mutex> lk(g_plans.mu);
     if (!P->pinned) {
@@ -385,7 +389,7 @@ nrx_status plan_upload(Plan *P, char *dst, hipStream_t st) {
       memcpy(P->pinned, P->blob.data(), P->meta_bytes);
     }
   }
-  HIPCHK(hipMemcpyAsync(dst, P->pinned, P->meta_bytes, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(dst, P->pinned, slots_only ? P->slot_bytes : P->meta_bytes, hipMemcpyHostToDevice, st));
   return NRX_OK;
 }
 
@@ -2001,7 +2005,7 @@ extern "C" nrx_status nrx_ls_estimate(const nrx_slot_desc *slots, int32_t n, con
   const FrontLayout L = front_layout(P, false);
   if (ws_bytes < L.total) return fail(NRX_ERR_WORKSPACE, "workspace %zu < required %zu bytes", ws_bytes, L.total);
   char *w = (char *)ws;
-  if (plan_upload(P, w + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
+  if (plan_upload(P, w + L.meta, st, true) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w + L.meta);
   float2 *pairs = (float2 *)(w + L.pairs);
   int64_t max_h = 0;
@@ -2028,7 +2032,7 @@ nrx_status lmmse_impl(const nrx_slot_desc *slots, int32_t n, int32_t m_max, cons
   const size_t need = L.total + align256(sizeof(SlotGeo) * (size_t)n);
   if (ws_bytes < need) return fail(NRX_ERR_WORKSPACE, "workspace %zu < required %zu bytes", ws_bytes, need);
   char *w = (char *)ws;
-  if (plan_upload(P, w + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
+  if (plan_upload(P, w + L.meta, st, true) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w + L.meta);
   float2 *pairs = (float2 *)(w + L.pairs);
   if (!h) launch_ls_pairs(D.geo, P->n, (int)P->max_pairs, (const float2 *)y, pairs, D.pair_off, st, slot_mask);
@@ -2192,7 +2196,7 @@ extern "C" nrx_status nrx_bce(const nrx_slot_desc *slots, int32_t n, int32_t m_m
   if (ws_bytes < need) return fail(NRX_ERR_WORKSPACE, "workspace %zu < required %zu bytes", ws_bytes, need);
   if (P->n_data_bits <= 0) return fail(NRX_ERR_SHAPE, "no data bits");
   char *w = (char *)ws;
-  if (plan_upload(P, w, st) != NRX_OK) return NRX_ERR_HIP;
+  if (plan_upload(P, w, st, true) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w);
   launch_bce(D.geo, nullptr, P->n, P->max_ute, m_max, llr, bits, dllr, (double *)(w + align256(P->meta_bytes)),
              (int)nb, loss, nerr, 1.0 / (double)P->n_data_bits, st);
@@ -2221,7 +2225,7 @@ extern "C" nrx_status nrx_mse(const nrx_slot_desc *slots, int32_t n, const float
   int64_t n_c = 0;   // complex entries of the batch
   for (auto &g : P->geo) n_c += (int64_t)g.S * 14 * g.U * g.B;
   char *w = (char *)ws;
-  if (plan_upload(P, w, st) != NRX_OK) return NRX_ERR_HIP;
+  if (plan_upload(P, w, st, true) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w);
   launch_mse(D.geo, P->n, h_est, h_true, dh_est, (float)(2.0 * (double)gamma / (double)n_c),
              (double *)(w + align256(P->meta_bytes)), (int)nb, loss, 1.0 / (double)n_c, st);
@@ -2288,7 +2292,7 @@ extern "C" nrx_status slot_sim(const nrx_sim_config *cfg, uint64_t seed, uint32_
   const SimLayout L = sim_layout(P);
   if (ws_bytes < L.total) return fail(NRX_ERR_WORKSPACE, "workspace %zu < required %zu bytes", ws_bytes, L.total);
   char *w = (char *)ws;
-  if (plan_upload(P, w + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
+  if (plan_upload(P, w + L.meta, st, true) != NRX_OK) return NRX_ERR_HIP;
   const Dev D = dev_tables(P, w + L.meta);
   float2 *dmrs = (float2 *)(w + L.dmrs);
   launch_dmrs(D.geo, P->n, dmrs, st);
