@@ -229,6 +229,13 @@ __host__ __device__ inline PersistIdx persist_decode(int it, int n_stages, int n
 int persist_max_grid();
 void launch_persist(const PersistArgs &a, int grid, hipStream_t st);
 // Clears n words (a fill kernel: no memset node in a captured graph).
+// copies up to two tables from pinned host memory to the device
+struct FetchSeg {
+  void *dst = nullptr;
+  const void *src = nullptr;
+  size_t bytes = 0;   // a multiple of 4
+};
+void launch_fetch(const FetchSeg &a, const FetchSeg &b, hipStream_t st);
 void launch_zero_words(unsigned int *p, int64_t n, hipStream_t st);
 
 // Slot simulator.

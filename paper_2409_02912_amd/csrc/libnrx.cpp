@@ -141,14 +141,14 @@ struct Plan {
   std::vector<char> blob;        // host image of the device tables
   void *pinned = nullptr;        // pinned copy, allocated on first upload
   ~Plan() {
-    // an asynchronous copy (or a graph replay) may still read the pinned tables
+    // a queued kernel (or a graph replay) may still read the pinned tables
     if (pinned) (void)hipDeviceSynchronize();
     if (pinned) (void)hipHostFree(pinned);
   }
 };
 using PlanRef = std::shared_ptr<Plan>;
 
-// A pinned host buffer; freed after the device has drained (an asynchronous copy may still read it).
+// A pinned host buffer; freed after the device has drained (a queued kernel may still read it).
 struct PinnedBuf {
   void *ptr = nullptr;
   size_t bytes = 0;
@@ -377,19 +377,21 @@ nrx_status get_plan(const nrx_slot_desc *d, int n, int max_ant, int m_max, int s
   return NRX_OK;
 }
 
-// Enqueues the copy of the plan's device tables into the workspace.  slots_only: without the lists of row tiles, which
-// only the network's kernels read (64 slots x 106 PRB, 4 UEs:
-// 2.9 MB, 60 us before the first kernel could start; one slot of 273 PRB, 2 UEs: 47 KB, 13 us).
-nrx_status plan_upload(Plan *P, char *dst, hipStream_t st, bool slots_only = false) {
+// Enqueues the copy of the plan's device tables (in pinned memory that every device can read) into the workspace.
+// slots_only: without the lists of row tiles, which only the network's kernels read (64 slots x 106 PRB, 4 UEs: 2.9 MB,
+// 60 us before the first kernel could start; one slot of 273 PRB, 2 UEs: 47 KB, 13 us).
+// A second table in pinned memory goes with it.
+nrx_status plan_upload(Plan *P, char *dst, hipStream_t st, bool slots_only = false, FetchSeg also = {}) {
   {
     std::lock_guard<std::mutex> lk(g_plans.mu);
     if (!P->pinned) {
-      if (hipHostMalloc(&P->pinned, P->meta_bytes, hipHostMallocDefault) != hipSuccess)
+      if (hipHostMalloc(&P->pinned, P->meta_bytes, hipHostMallocPortable) != hipSuccess)
         return fail(NRX_ERR_HIP, "hipHostMalloc of %zu bytes failed", P->meta_bytes);
       memcpy(P->pinned, P->blob.data(), P->meta_bytes);
     }
   }
-  HIPCHK(hipMemcpyAsync(dst, P->pinned, slots_only ? P->slot_bytes : P->meta_bytes, hipMemcpyHostToDevice, st));
+  launch_fetch({dst, P->pinned, slots_only ? P->slot_bytes : P->meta_bytes}, also, st);
+  HIPCHK(hipGetLastError());
   return NRX_OK;
 }
 
@@ -771,6 +773,7 @@ extern "C" nrx_status nrx_model_destroy(nrx_model *m) {
     if (m->graphs->cap) (void)hipStreamDestroy(m->graphs->cap);
     delete m->graphs;
   }
+  if (m->pinned_jobs || m->pinned_bjobs) (void)hipDeviceSynchronize();   // no kernel may still read the job tables
   if (m->pinned_bjobs) (void)hipHostFree(m->pinned_bjobs);
   for (auto &e : m->pending) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
   for (auto e : m->pool) (void)hipEventDestroy(e);
@@ -935,7 +938,7 @@ struct ProfMark {
 nrx_status model_pinned(nrx_model *m) {
   std::lock_guard<std::mutex> lk(m->mu);
   if (m->pinned_jobs) return NRX_OK;
-  if (hipHostMalloc(&m->pinned_jobs, sizeof(PrepJob) * m->jobs.size(), hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc(&m->pinned_jobs, sizeof(PrepJob) * m->jobs.size(), hipHostMallocPortable) != hipSuccess)
     return fail(NRX_ERR_HIP, "hipHostMalloc failed");
   memcpy(m->pinned_jobs, m->jobs.data(), sizeof(PrepJob) * m->jobs.size());
   return NRX_OK;
@@ -979,7 +982,7 @@ std::shared_ptr<PinnedBuf> persist_table(nrx_model *m, const std::vector<Persist
     m->ptables.erase(lru);   // a graph that captured it keeps its own reference
   }
   auto b = std::make_shared<PinnedBuf>();
-  if (hipHostMalloc(&b->ptr, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
+  if (hipHostMalloc(&b->ptr, bytes, hipHostMallocPortable) != hipSuccess) return nullptr;
   b->bytes = bytes;
   memcpy(b->ptr, pst.data(), bytes);
   m->ptables[key] = nrx_model::PTable{b, ++m->ptable_tick};
@@ -993,8 +996,9 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
                         float *hest = nullptr, int64_t h_stride = 0) {
   nrx_status ps = model_pinned(m);
   if (ps != NRX_OK) return ps;
-  if (plan_upload(const_cast<Plan *>(P), ws + L.meta, st) != NRX_OK) return NRX_ERR_HIP;
-  HIPCHK(hipMemcpyAsync(ws + L.jobs, m->pinned_jobs, sizeof(PrepJob) * m->jobs.size(), hipMemcpyHostToDevice, st));
+  if (plan_upload(const_cast<Plan *>(P), ws + L.meta, st, false,
+                  {ws + L.jobs, m->pinned_jobs, sizeof(PrepJob) * m->jobs.size()}) != NRX_OK)
+    return NRX_ERR_HIP;
   const Dev D = dev_tables(P, ws + L.meta);
   T *wprep = (T *)(ws + L.wprep);
   float *fields = (float *)(ws + L.fields);
@@ -1030,8 +1034,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
   if (f8) {
     if (!m->calibrated) return fail(NRX_ERR_INVALID, "FP8 model has no activation scales (nrx_calibrate)");
     ProfMark pm(m, NRX_K_FRONTEND, st);
-    HIPCHK(hipMemcpyAsync(ws + L.f8jobs, m->pinned_fp8jobs, sizeof(Fp8Job) * m->fp8jobs.size(),
-                          hipMemcpyHostToDevice, st));
+    launch_fetch({ws + L.f8jobs, m->pinned_fp8jobs, sizeof(Fp8Job) * m->fp8jobs.size()}, {}, st);
     launch_prep_fp8(w, (const Fp8Job *)(ws + L.f8jobs), (int)m->fp8jobs.size(), (uint8_t *)(ws + L.w8),
                     (float *)(ws + L.wsc), st);
   }
@@ -1279,7 +1282,7 @@ nrx_status forward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const f
     if (grid <= 0) return fail(NRX_ERR_UNSUPPORTED, "the persistent forward kernel does not fit on this device");
     std::shared_ptr<PinnedBuf> tab = persist_table(m, pst);
     if (!tab) return fail(NRX_ERR_HIP, "hipHostMalloc of the persistent stage table failed");
-    HIPCHK(hipMemcpyAsync(ws + L.pstages, tab->ptr, tab->bytes, hipMemcpyHostToDevice, st));
+    launch_fetch({ws + L.pstages, tab->ptr, tab->bytes}, {}, st);
     const int64_t n_tiles = P->ptile_base.back();
     unsigned int *ctl = (unsigned int *)(ws + L.pctl);
     launch_zero_words(ctl, 64 + (int64_t)pst.size() * n_tiles, st);
@@ -1458,7 +1461,7 @@ nrx_status graph_forward(nrx_model *m, const PlanRef &PR, const GraphKey &key, F
     {
       std::lock_guard<std::mutex> lk(g_plans.mu);
       if (!P->pinned) {
-        if (hipHostMalloc(&P->pinned, P->meta_bytes, hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(&P->pinned, P->meta_bytes, hipHostMallocPortable) != hipSuccess)
           return fail(NRX_ERR_HIP, "hipHostMalloc failed");
         memcpy(P->pinned, P->blob.data(), P->meta_bytes);
       }
@@ -1699,12 +1702,12 @@ nrx_status backward_impl(nrx_model *m, const Plan *P, const FwdLayout &L, const 
   {
     std::lock_guard<std::mutex> lk(m->mu);
     if (!m->pinned_bjobs) {
-      if (hipHostMalloc(&m->pinned_bjobs, sizeof(PrepJob) * m->bjobs.size(), hipHostMallocDefault) != hipSuccess)
+      if (hipHostMalloc(&m->pinned_bjobs, sizeof(PrepJob) * m->bjobs.size(), hipHostMallocPortable) != hipSuccess)
         return fail(NRX_ERR_HIP, "hipHostMalloc failed");
       memcpy(m->pinned_bjobs, m->bjobs.data(), sizeof(PrepJob) * m->bjobs.size());
     }
   }
-  HIPCHK(hipMemcpyAsync(ws + L.bjobs, m->pinned_bjobs, sizeof(PrepJob) * m->bjobs.size(), hipMemcpyHostToDevice, st));
+  launch_fetch({ws + L.bjobs, m->pinned_bjobs, sizeof(PrepJob) * m->bjobs.size()}, {}, st);
   const Dev D = dev_tables(P, ws + L.meta);
   T *bp = (T *)(ws + L.bprep);
   launch_prep<T>(w, (const PrepJob *)(ws + L.bjobs), (int)m->bjobs.size(), m->bprep_units, bp, nullptr, st);
@@ -2330,7 +2333,7 @@ nrx_status build_fp8_jobs(nrx_model *m) {
     jobs.push_back(Fp8Job{B.b.w, B.b.cin_real, B.b.cin_total, NRX_D, m->act_scale[C + i], 1.0f, B.b.w8, B.b.ws8});
   }
   void *p = nullptr;
-  if (hipHostMalloc(&p, sizeof(Fp8Job) * jobs.size(), hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc(&p, sizeof(Fp8Job) * jobs.size(), hipHostMallocPortable) != hipSuccess)
     return fail(NRX_ERR_HIP, "hipHostMalloc failed");
   memcpy(p, jobs.data(), sizeof(Fp8Job) * jobs.size());
   std::lock_guard<std::mutex> lk(m->mu);
