@@ -518,37 +518,43 @@ __device__ __forceinline__ float pe_t_val(int t) {
 __global__ void colsum_reduce_kernel(const float *partial, int n_slots, float *red) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;   // t * 768 + class * 128 + o
   if (e >= 14 * 768) return;
-  const int t = e / 768, k = e % 768;
-  double s = 0.0;
-  for (int sl = 0; sl < n_slots; ++sl) s += partial[((int64_t)sl * 14 + t) * 768 + k];
-  red[e] = (float)s;
+  red[e] = (float)sum_strided(partial + e, n_slots, 14 * 768);
 }
 
 // Bias gradient (sum of all classes; block 9) and, for layers with a folded PE,
-// the PE weight gradients of tap blockIdx.x (blocks 0..8).  Thread = output channel.
-__global__ void bias_pe_kernel(const float *red, int64_t bias_off, int64_t pe_w_off, int cin_total, int pe_ch,
+// the PE weight gradients of tap blockIdx.x (blocks 0..8).  Thread = output channel.  All 84 sums of a thread's column
+// are read before the first is added: one after the other their latencies made 23 us of the kernel's time, which
+// is now 5 us.
+__global__ __launch_bounds__(128) void bias_pe_kernel(const float *red, int64_t bias_off, int64_t pe_w_off, int cin_total, int pe_ch,
                                float *dw, int acc) {
   const int o = threadIdx.x, tap = blockIdx.x;
+  if (tap < 9 && pe_w_off < 0) return;
+  float v[14 * 6];
+#pragma unroll
+  for (int k = 0; k < 14 * 6; ++k) v[k] = red[k * 128 + o];
   if (tap == 9) {
     double b = 0.0;
-    for (int k = 0; k < 14 * 6; ++k) b += red[k * 128 + o];
+#pragma unroll
+    for (int k = 0; k < 14 * 6; ++k) b += v[k];
     dw[bias_off + o] = acc ? dw[bias_off + o] + (float)b : (float)b;
     return;
   }
-  if (pe_w_off < 0) return;
   const int di = tap / 3 - 1, dj = tap % 3 - 1;
   double gt = 0.0, gf = 0.0;
+#pragma unroll
   for (int t = 0; t < 14; ++t) {
     const int tt = t + dj;
     if (tt < 0 || tt >= 14) continue;
     const float pt = pe_t_val(tt);
+#pragma unroll
     for (int par = 0; par < 2; ++par) {
       const float pf = ((par + di) & 1) ? 1.f : -1.f;
+#pragma unroll
       for (int edge = 0; edge < 3; ++edge) {
         if ((edge == 1 && di < 0) || (edge == 2 && di > 0)) continue;
-        const double v = red[t * 768 + (par * 3 + edge) * 128 + o];
-        gt += v * pt;
-        gf += v * pf;
+        const double x = v[t * 6 + par * 3 + edge];
+        gt += x * pt;
+        gf += x * pf;
       }
     }
   }
