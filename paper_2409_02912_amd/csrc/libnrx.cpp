@@ -76,7 +76,10 @@ int conv_mb(const std::vector<Tile> *ct, double over, int max_mb) {
   }
   return best;
 }
-constexpr double CONV_OVER_NARROW = 5.0;   // 64-channel rows: a tap's weights, not its products, are most of a round
+// 64-channel rows: a tap's weights, not its products, are most of a round.  us for mb = 4 / 3 / 2 / 1 of a pass of 8 blocks:
+// 8,064 rows 375 / 316 / 268 / 219; 44,352 rows 436 / 375 / 326 / 330; 88,704 rows 471 / 418 / 531 / 517; 183,456 rows
+// 829 / 713 / 770 / 741; 354,816 rows 1194 / 1242 / 1365 / 1323.  The rule takes the fastest of each.
+constexpr double CONV_OVER_NARROW = 5.0;
 constexpr double CONV_OVER_SPLIT = 0.3;    // FP32 by BF16 parts
 constexpr int CONV_SPLIT_MB = 3;           // (512-row tiles would spill the parts of their fragments)
 template <typename T>

@@ -69,6 +69,26 @@ def test_lmmse_edges(name, given):
         assert np.all(got[:, list(nr.DMRS_SYMBOLS)] == 0)
 
 
+@pytest.mark.parametrize("n_ant", [7, 8, 9, 11, 15])
+def test_lmmse_antenna_groups(n_ant):
+    """Samples are read eight antennas at a time, then in pairs, then singly: every way the count can end, with slots of
+    one UE and of four beside each other.  Bar as above."""
+    shapes = [_shape(2, n_ant, 4, [4, 2, 8, 6], 5), _shape(3, n_ant, 1, [6], 9)]
+    log(f"lmmse antenna groups: {n_ant}")
+    ref = _oracle(shapes, 24)
+    shapes = [dict(s, n0=r["n0_32"]) for s, r in zip(shapes, ref)]
+    descs, sz = L.make_slots(shapes, 8)
+    y = torch.from_numpy(pack_complex([r["y32"] for r in ref])).cuda()
+    llr = torch.full((sz["llr"],), float("nan"), device="cuda")
+    ws = torch.empty(L.lmmse_workspace_bytes(descs), dtype=torch.uint8, device="cuda")
+    L.lmmse_demap(descs, 8, y, llr, ws)
+    torch.cuda.synchronize()
+    for got, r in zip(split_llr(llr.cpu().numpy(), shapes, 8), ref):
+        exp = receiver.lmmse_demap(r["y32"], receiver.ls_estimate(r["y32"], r["desc"]), r["n0_32"], r["desc"], 8)
+        for u in range(exp.shape[0]):
+            assert rel_err(got[u], exp[u]) < 1e-5, u
+
+
 def test_nothing_beside_the_batch_is_written():
     """The LLR array is exactly covered: guard words on both sides of a one-PRB slot keep their values."""
     shapes = [_shape(1, 2, 3, [2, 4, 2], 2)]
